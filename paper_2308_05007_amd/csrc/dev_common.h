@@ -10,6 +10,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace rwmi {
 
 // ------------------------------------------------------------------ lattice
@@ -67,6 +69,15 @@ __host__ __device__ __forceinline__ size_t fidx(bool tiled, int slot, uint32_t n
 }
 __host__ __device__ __forceinline__ uint64_t f_elems(int64_t N) {
   return (uint64_t)((N + (int64_t)kTile - 1) >> kTileShift) * (uint64_t)kQ * (uint64_t)kTile;
+}
+
+// f(0), f(1), ... with compile-time indices.
+template <int I, int N_, typename F>
+__device__ __forceinline__ void unroll(F&& f) {
+  if constexpr (I < N_) {
+    f(std::integral_constant<int, I>{});
+    unroll<I + 1, N_>(f);
+  }
 }
 
 constexpr int kMaxParticles = 64;

@@ -326,14 +326,6 @@ __device__ __forceinline__ R edot_c(R ax, R ay, R az) {
   return s;
 }
 
-template <int I, int N_, typename F>
-__device__ __forceinline__ void unroll(F&& f) {
-  if constexpr (I < N_) {
-    f(std::integral_constant<int, I>{});
-    unroll<I + 1, N_>(f);
-  }
-}
-
 // Lattice layouts of a step: two lattices, or one lattice streamed in place
 // at an even or an odd step (the slots a step reads and writes).
 enum Layout { kTwoLattices = 0, kInPlaceEven = 1, kInPlaceOdd = 2 };
