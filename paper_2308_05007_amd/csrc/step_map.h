@@ -9,8 +9,9 @@
 //
 // Hardware block i runs on XCD i mod 8.  With the XCD-aware map every XCD
 // receives a contiguous run of the fluid blocks (neighbouring nodes share its
-// L2), its share of the walker blocks interleaved evenly among them (latency-
-// bound walker work overlaps bandwidth-bound fluid work on every CU), and its
+// L2), its share of the walker blocks interleaved evenly among all but the last
+// of them (latency-bound walker work overlaps bandwidth-bound fluid work on
+// every CU, and fluid blocks cover the end of the last walkers), and its
 // prologue blocks first.  Without it the roles are dealt the same way over the
 // whole grid.
 #pragma once
@@ -39,6 +40,17 @@ constexpr int kFlagDem = 8;
 // The domains couple fluid and particles by interpolated bounce-back
 // (lbm_impl.h); set by the host.
 constexpr int kFlagIbb = 16;
+
+// The last positions of an XCD's run hold fluid blocks only: a walker block
+// can end with a chain of near-surface evaluations (up to 10-20 us), which
+// would otherwise run on alone after the last fluid blocks.  448 is twice the
+// blocks of 256 threads an XCD holds at once (32 CUs, 7 blocks), some 12 us of
+// fluid.  us per step with the walkers spread over the whole run, and with the
+// last 224, 448 and 896 positions left out: 128^3 FP32 channel 65.9, 62.7,
+// 61.5, 65.9; 192^3 FP32 bounce-back 297.4, 293.7, 290.9, 291.3; 80^3 FP32
+// 26.1, 23.5, 24.0, 24.0; 97x61x83 FP64 41.6, 35.5, 35.7, 35.7; 256^3 within
+// 1%.  (Walkers all first, which the smallest grids get: they fit the chip.)
+constexpr int kTailBlocks = 448;
 
 struct DomView;
 
@@ -88,10 +100,16 @@ RWMI_HD inline int step_role(int i, const int nb[3], bool xcd, int& idx) {
   }
   const int h = g - cp, T = cw + cf;
   if (h >= T) return kRoleNone;
-  // walker blocks spread evenly among the fluid blocks: position h is a
-  // walker block when floor((h+1) cw / T) > floor(h cw / T)
-  const int wa = (int)(((int64_t)h * cw) / T);
-  const int wb = (int)(((int64_t)(h + 1) * cw) / T);
+  // walker blocks spread evenly over the first S positions: position h < S is
+  // a walker block when floor((h+1) cw / S) > floor(h cw / S)
+  const int tail = xcd ? kTailBlocks : 8 * kTailBlocks;
+  const int S = T - tail > cw ? T - tail : cw;
+  if (h >= S) {
+    idx = bf + (h - cw);
+    return kRoleFluid;
+  }
+  const int wa = (int)(((int64_t)h * cw) / S);
+  const int wb = (int)(((int64_t)(h + 1) * cw) / S);
   if (wb > wa) {
     idx = bw + wa;
     return kRoleWalk;
