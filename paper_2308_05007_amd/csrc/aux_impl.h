@@ -159,88 +159,197 @@ __global__ void __launch_bounds__(kProfileThreads) k_profile(const DomView* __re
 }
 
 // ---------------------------------------------------------------- moments
-// Deterministic FP64 reductions: chunk k covers elements [k*4096, (k+1)*4096);
-// thread j of the 256-thread block adds elements j, j+256, ... in order, the
-// block then folds the 256 partials by halving; the final kernel adds the
-// chunk partials in chunk order.  The result does not depend on the launch
-// configuration of the stepping kernels.
-constexpr int kRedChunk = 4096;
-constexpr int kRedThreads = 256;
-constexpr int kWalkMom = 6;   // sum d[3], sum d^2[3]
-constexpr int kNodeMom = 12;  // rho, rho u[3], (1-eps) u[3], (1-eps), eps us[3], eps
+// FP64 reductions whose results do not depend on the launch configuration of
+// the stepping kernels, nor on the order of the walkers' slots (which the
+// regrouping leaves arbitrary within a bin).
+//
+// Nodes: chunk k covers nodes [k*4096, (k+1)*4096), one block each; thread j
+// of its T threads adds nodes j, j+T, ..., the block's sums are folded in a
+// fixed order, and the final kernel adds the chunks the same way.  T is 1024 on
+// a small lattice, whose few blocks would leave the chip idle with fewer, and
+// 256 on a large one, where a block's other threads wait for the wave that
+// culls the particles (launch_moments).
+//
+// Walkers: their sums are exact, so any order gives the same result: every
+// term is split into three integers (ExactSum), the integers are added, and
+// one rounding at the end makes the double.  Walkers are so read slot by slot,
+// coalesced.  In id order (a gather through the id map, 28 scattered bytes a
+// walker) the same sums took 1.19 ms for 1e7 walkers, and the map 0.13 ms.
+constexpr int kRedThreads = 1024;
+constexpr int kRedRows = kRedThreads / 16;
+constexpr int kRedChunk = 4096;       // nodes per block
+constexpr int kWalkChunk = 16384;     // walkers per block
+constexpr int kWalkMom = 6;           // sum d[3], sum d^2[3]
+constexpr int kWalkWords = 3 * kWalkMom;
+constexpr int kNodeMom = 12;          // rho, rho u[3], (1-eps) u[3], (1-eps), eps us[3], eps
 
-template <int K>
-__device__ __forceinline__ void block_fold(double (*sh)[kRedThreads], double acc[K], double* out) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < K; ++k) sh[k][tid] = acc[k];
-  __syncthreads();
-  for (int h = kRedThreads / 2; h > 0; h >>= 1) {
-    if (tid < h) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) sh[k][tid] = sh[k][tid] + sh[k][tid + h];
-    }
-    __syncthreads();
+// Sum of doubles below 2^81 in magnitude, exact to 2^-59 per term: x = h 2^30
+// + m 2^-10 + l 2^-59 with each remainder exact (powers of two only), |m| <=
+// 2^39, |l| <= 2^48.  `carry` brings the digits back to those ranges, so that
+// 2^14 terms, or 2^14 carried sums, fit in 64 bits.
+struct ExactSum {
+  long long h = 0, m = 0, l = 0;
+  // the nearest integer to t (|t| < 2^51) as the low bits of t + 1.5 2^52
+  static __device__ __forceinline__ long long digit(double& t) {
+    constexpr double magic = 0x1.8p52;
+    const double s = t + magic;
+    t = s - magic;
+    return __double_as_longlong(s) - __double_as_longlong(magic);
   }
-  if (tid < K) out[tid] = sh[tid][0];
+  __device__ __forceinline__ void add(double x) {
+    double t = x * 0x1p-30;
+    h += digit(t);
+    x = x - t * 0x1p30;
+    t = x * 0x1p10;
+    m += digit(t);
+    x = x - t * 0x1p-10;
+    t = x * 0x1p59;
+    l += digit(t);
+  }
+  __device__ __forceinline__ void carry() {
+    const long long c = (l + (1ll << 48)) >> 49;
+    l -= c << 49;
+    m += c;
+    const long long d = (m + (1ll << 39)) >> 40;
+    m -= d << 40;
+    h += d;
+  }
+  __device__ __forceinline__ double value() {
+    carry();
+    return (double)h * 0x1p30 + ((double)m * 0x1p-10 + (double)l * 0x1p-59);
+  }
+};
+
+// Value of the lane N places on, around the row of 16 lanes.
+template <int N, typename T>
+__device__ __forceinline__ T row_ror(T v) {
+  static_assert(sizeof(T) == 8, "two words");
+  union { T t; int i[2]; } x;
+  x.t = v;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) x.i[k] = __builtin_amdgcn_update_dpp(0, x.i[k], 0x120 + N, 0xf, 0xf, true);
+  return x.t;
+}
+template <typename T>
+__device__ __forceinline__ T row_sum(T v) {
+  v = v + row_ror<8>(v);
+  v = v + row_ror<4>(v);
+  v = v + row_ror<2>(v);
+  return v + row_ror<1>(v);
 }
 
+// Sums over the block of acc[0..K) of every thread, in thread 16 k for k < K.
+// The order is fixed: each row of 16 lanes through the DPP network, the rows'
+// sums through LDS, thread 16 k + i adding rows i, i + 16, ..., then their row.
+template <int THREADS, typename T, int K>
+__device__ __forceinline__ T block_sum(T (&acc)[K], T (*sh)[K]) {
+  static_assert(16 * K <= THREADS, "a row per sum");
+#pragma unroll
+  for (int k = 0; k < K; ++k) acc[k] = row_sum(acc[k]);
+  const int tid = threadIdx.x;
+  if ((tid & 15) == 0)
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[tid >> 4][k] = acc[k];
+  __syncthreads();
+  T s = (T)0;
+  if (tid < 16 * K) {
+#pragma unroll
+    for (int r = 0; r < THREADS / 256; ++r) s = s + sh[(tid & 15) + 16 * r][tid >> 4];
+    s = row_sum(s);
+  }
+  __syncthreads();
+  return s;
+}
+
+struct MomRef {
+  double x[3];
+};
+
+// part[chunk][3 k + digit]: the chunk's carried sums.
 template <typename R>
-__global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __restrict__ views, int dom,
-                                                             const double* __restrict__ ref, double* __restrict__ part) {
-  __shared__ double sh[kWalkMom][kRedThreads];
+__global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __restrict__ views, int dom, MomRef ref,
+                                                             long long* __restrict__ part) {
+  __shared__ long long sh[kRedRows][kWalkWords];
   const DomView& V = views[dom];
-  const R* off = (const R*)V.woff;
-  const int64_t base = (int64_t)blockIdx.x * kRedChunk;
-  double acc[kWalkMom] = {0, 0, 0, 0, 0, 0};
-  const int nx = V.n[0], ny = V.n[1];
-  for (int j = threadIdx.x; j < kRedChunk; j += kRedThreads) {
-    const int64_t id = base + j;  // walker ids in order, whatever slot holds them
-    if (id >= V.nw) break;
-    const int64_t w = V.winv[id];
-    const int32_t lc = V.wcell[w];
-    const int c[3] = {lc % nx, (lc / nx) % ny, lc / (nx * ny)};
+  const auto off = gp((const R*)V.woff);
+  const auto img = gp((const int32_t*)V.wimg);
+  const auto cell = gp((const int32_t*)V.wcell);
+  const int64_t nw = V.nw, base = (int64_t)blockIdx.x * kWalkChunk;
+  ExactSum sum[kWalkMom];
+#pragma unroll 4
+  for (int j = 0; j < kWalkChunk / kRedThreads; ++j) {
+    const int64_t w = base + (int64_t)j * kRedThreads + threadIdx.x;
+    if (w >= nw) break;
+    const uint32_t lc = (uint32_t)cell[w];
+    const uint32_t q1 = fdiv(lc, V.dx);
+    const int cz = (int)fdiv(q1, V.dy);
+    const int c[3] = {(int)(lc - q1 * (uint32_t)V.n[0]), (int)q1 - cz * V.n[1], cz};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const int64_t X = (int64_t)c[a] + (int64_t)V.wimg[a * V.nw + w] * (int64_t)V.n[a];
-      const double dv = ((double)X - ref[a]) + (double)off[a * V.nw + w];
-      acc[a] = acc[a] + dv;
-      acc[3 + a] = acc[3 + a] + dv * dv;
+      const int64_t X = (int64_t)c[a] + (int64_t)img[a * nw + w] * (int64_t)V.n[a];
+      const double dv = ((double)X - ref.x[a]) + (double)off[a * nw + w];
+      sum[a].add(dv);
+      sum[3 + a].add(dv * dv);
     }
   }
-  block_fold<kWalkMom>(sh, acc, part + (int64_t)blockIdx.x * kWalkMom);
+  long long acc[kWalkWords];
+#pragma unroll
+  for (int k = 0; k < kWalkMom; ++k) {
+    acc[3 * k] = sum[k].h;
+    acc[3 * k + 1] = sum[k].m;
+    acc[3 * k + 2] = sum[k].l;
+  }
+  const long long s = block_sum<kRedThreads>(acc, sh);
+  if ((threadIdx.x & 15) == 0 && threadIdx.x < 16 * kWalkWords) sh[0][threadIdx.x >> 4] = s;
+  __syncthreads();
+  if (threadIdx.x < kWalkMom) {
+    ExactSum e;
+    e.h = sh[0][3 * threadIdx.x];
+    e.m = sh[0][3 * threadIdx.x + 1];
+    e.l = sh[0][3 * threadIdx.x + 2];
+    e.carry();
+    long long* o = part + (int64_t)blockIdx.x * kWalkWords + 3 * threadIdx.x;
+    o[0] = e.h;
+    o[1] = e.m;
+    o[2] = e.l;
+  }
 }
 
-template <typename U>
-__global__ void __launch_bounds__(kRedThreads) k_mom_nodes(const DomView* __restrict__ views, int dom,
+template <typename U, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict__ views, int dom,
                                                            double* __restrict__ part) {
-  __shared__ double sh[kNodeMom][kRedThreads];
+  __shared__ double sh[THREADS / 16][kNodeMom];
   using C = typename Store<sizeof(U) == 8 ? P64 : P32>::C;
   __shared__ BlockParticles<C> sp;
   const DomView& V = views[dom];
-  const int64_t base = (int64_t)blockIdx.x * kRedChunk;
-  const int64_t last = (base + kRedChunk - 1 < V.N) ? base + kRedChunk - 1 : V.N - 1;
+  const uint32_t N = (uint32_t)V.N;
+  const uint32_t base = blockIdx.x * (uint32_t)kRedChunk;
+  const uint32_t last = base + kRedChunk - 1 < N ? base + kRedChunk - 1 : N - 1;
   const uint64_t done = V.tstep[0];  // steps completed
   const bool stepped = done > 0;
-  // coupled particles: poses from the table the particle update wrote
-  if (stepped && V.np > 0) cull_block<C>(V, (uint32_t)base, (uint32_t)last, done - 1, sp, V.dem_mask != 0ull);
+  // the poses of the last step are still in the table its prologue (or, for
+  // coupled particles, the particle update) wrote
+  if (stepped && V.np > 0 && !V.ibb) cull_block<C>(V, base, last, done - 1, sp, true);
   else if (threadIdx.x == 0) sp.cnt = 0;
   __syncthreads();
   double acc[kNodeMom];
 #pragma unroll
   for (int k = 0; k < kNodeMom; ++k) acc[k] = 0.0;
-  const U* uf = (const U*)V.u[stepped ? ((done - 1) & 1ull) : 0];
-  const U* rf = (const U*)V.rho;
-  const int nx = V.n[0], ny = V.n[1];
-  for (int j = threadIdx.x; j < kRedChunk; j += kRedThreads) {
-    const int64_t id = base + j;
-    if (id >= V.N) break;
-    const int nd[3] = {(int)(id % nx), (int)((id / nx) % ny), (int)(id / ((int64_t)nx * ny))};
+  const auto uf = gp((const U*)V.u[stepped ? ((done - 1) & 1ull) : 0]);
+  const auto rf = gp((const U*)V.rho);
+  for (int j = 0; j < kRedChunk / THREADS; ++j) {
+    const uint32_t id = base + (uint32_t)j * THREADS + threadIdx.x;
+    if (id >= N) break;
+    const uint32_t q1 = fdiv(id, V.dx);
+    const int z = (int)fdiv(q1, V.dy);
+    const int nd[3] = {(int)(id - q1 * (uint32_t)V.n[0]), (int)q1 - z * V.n[1], z};
     bool wall = false;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
       if (V.bc[a] && (nd[a] == 0 || nd[a] == V.n[a] - 1)) wall = true;
     if (wall) continue;
+    const double u[3] = {(double)uf[3ull * id], (double)uf[3ull * id + 1], (double)uf[3ull * id + 2]};
+    const double r = (double)rf[id];
     double es = 0.0, un[3] = {0.0, 0.0, 0.0};
     if (V.ibb) {
       // interpolated bounce-back: a node is solid or fluid; a solid node's
@@ -248,7 +357,7 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_nodes(const DomView* __rest
       if (stepped && (V.smap[(done - 1) & 1ull][id] & kSolidBits)) {
         es = 1.0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) un[a] = (double)uf[3 * id + a];
+        for (int a = 0; a < 3; ++a) un[a] = u[a];
       }
     } else
     for (int k = 0; k < sp.cnt; ++k) {
@@ -264,41 +373,60 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_nodes(const DomView* __rest
       for (int a = 0; a < 3; ++a) un[a] = un[a] + e * up[a];
     }
     const double eps = es < 1.0 ? es : 1.0;
-    const double r = (double)rf[id];
     acc[0] = acc[0] + r;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double ua = (double)uf[3 * id + a];
       const double usa = es > 0.0 ? un[a] / es : 0.0;
-      acc[1 + a] = acc[1 + a] + r * ua;
-      acc[4 + a] = acc[4 + a] + (1.0 - eps) * ua;
+      acc[1 + a] = acc[1 + a] + r * u[a];
+      acc[4 + a] = acc[4 + a] + (1.0 - eps) * u[a];
       acc[8 + a] = acc[8 + a] + eps * usa;
     }
     acc[7] = acc[7] + (1.0 - eps);
     acc[11] = acc[11] + eps;
   }
-  block_fold<kNodeMom>(sh, acc, part + (int64_t)blockIdx.x * kNodeMom);
+  const double s = block_sum<THREADS>(acc, sh);
+  if ((threadIdx.x & 15) == 0 && threadIdx.x < 16 * kNodeMom)
+    part[(int64_t)blockIdx.x * kNodeMom + (threadIdx.x >> 4)] = s;
 }
 
-// out: [0..5] walker sums, [6..17] node sums, [18..25] counters, [26] step
-__global__ void k_mom_final(const DomView* __restrict__ views, int dom, const double* __restrict__ pw, int64_t nbw,
-                            const double* __restrict__ pn, int64_t nbn, double* __restrict__ out) {
+// out: [0..5] walker sums, [6..17] node sums, [18..25] counters, [26] step.
+// One block; one thread adding the chunks in turn took 1.2 ms for the 4096
+// chunks of a 256^3 lattice.
+__global__ void __launch_bounds__(kRedThreads) k_mom_final(const DomView* __restrict__ views, int dom,
+                                                           const long long* __restrict__ pw, int64_t nbw,
+                                                           const double* __restrict__ pn, int64_t nbn,
+                                                           double* __restrict__ out) {
+  __shared__ long long shw[kRedRows][kWalkWords];
+  __shared__ double shn[kRedRows][kNodeMom];
   const DomView& V = views[dom];
   const int tid = threadIdx.x;
+  long long aw[kWalkWords];
+#pragma unroll
+  for (int k = 0; k < kWalkWords; ++k) aw[k] = 0;
+  for (int64_t b = tid; b < nbw; b += kRedThreads)
+#pragma unroll
+    for (int k = 0; k < kWalkWords; ++k) aw[k] += gp(pw)[b * kWalkWords + k];
+  double an[kNodeMom];
+#pragma unroll
+  for (int k = 0; k < kNodeMom; ++k) an[k] = 0.0;
+  for (int64_t b = tid; b < nbn; b += kRedThreads)
+#pragma unroll
+    for (int k = 0; k < kNodeMom; ++k) an[k] = an[k] + gp(pn)[b * kNodeMom + k];
+  const long long sw = block_sum<kRedThreads>(aw, shw);
+  if ((tid & 15) == 0 && tid < 16 * kWalkWords) shw[0][tid >> 4] = sw;
+  const double sn = block_sum<kRedThreads>(an, shn);
+  if ((tid & 15) == 0 && tid < 16 * kNodeMom) out[kWalkMom + (tid >> 4)] = sn;
+  __syncthreads();
   if (tid < kWalkMom) {
-    double s = 0.0;
-    for (int64_t b = 0; b < nbw; ++b) s = s + pw[b * kWalkMom + tid];
-    out[tid] = s;
-  } else if (tid < kWalkMom + kNodeMom) {
-    const int k = tid - kWalkMom;
-    double s = 0.0;
-    for (int64_t b = 0; b < nbn; ++b) s = s + pn[b * kNodeMom + k];
-    out[tid] = s;
-  } else if (tid < kWalkMom + kNodeMom + kCounters) {
-    const int k = tid - kWalkMom - kNodeMom;
-    out[tid] = __longlong_as_double((long long)V.counters[k]);
-  } else if (tid == kWalkMom + kNodeMom + kCounters) {
-    out[tid] = __longlong_as_double((long long)V.tstep[0]);
+    ExactSum e;
+    e.h = shw[0][3 * tid];
+    e.m = shw[0][3 * tid + 1];
+    e.l = shw[0][3 * tid + 2];
+    out[tid] = e.value();
+  } else if (tid >= 64 && tid < 64 + kCounters) {
+    out[kWalkMom + kNodeMom + tid - 64] = __longlong_as_double((long long)V.counters[tid - 64]);
+  } else if (tid == 64 + kCounters) {
+    out[kWalkMom + kNodeMom + kCounters] = __longlong_as_double((long long)V.tstep[0]);
   }
 }
 

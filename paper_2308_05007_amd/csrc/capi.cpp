@@ -114,7 +114,6 @@ struct rwmi_domain {
   double* mom_part = nullptr;
   size_t mom_part_n = 0;
   double* mom_out = nullptr;
-  double* dref = nullptr;
   rwmi_batch* batch = nullptr;
   // two-way coupled particles
   bool dem = false;
@@ -1303,7 +1302,8 @@ rwmi_status rwmi_read_moments(rwmi_domain* d, rwmi_moments* out) {
   rwmi_status st;
   if ((st = finalize_particles(d)) != RWMI_OK) return st;
   const int64_t N = d->hv.N, nw = d->hv.nw;
-  const size_t need = 6 * ((nw + 4095) / 4096) + 12 * ((N + 4095) / 4096) + 8;
+  const size_t words = rwmi::moment_walker_words(nw);
+  const size_t need = words + 12 * ((N + 4095) / 4096);
   if (d->mom_part_n < need) {
     release(d, d->mom_part);
     d->mom_part = nullptr;
@@ -1311,11 +1311,8 @@ rwmi_status rwmi_read_moments(rwmi_domain* d, rwmi_moments* out) {
     d->mom_part_n = need;
   }
   if (!d->mom_out && (st = alloc_into(d, d->mom_out, 8 * 32)) != RWMI_OK) return st;
-  if (!d->dref && (st = alloc_into(d, d->dref, 8 * 4)) != RWMI_OK) return st;
-  HIPCHK(d, hipMemcpyAsync(d->dref, d->ref, 24, hipMemcpyHostToDevice, d->stream));
-  double* pw = d->mom_part;
-  double* pn = d->mom_part + 6 * ((nw + 4095) / 4096);
-  HIPCHK(d, rwmi::launch_moments(d->prec, d->dv, 0, N, nw, d->dref, pw, pn, d->mom_out, d->stream));
+  HIPCHK(d, rwmi::launch_moments(d->prec, d->dv, 0, N, nw, d->ref, d->mom_part, d->mom_part + words, d->mom_out,
+                                 d->stream));
   double h[32];
   HIPCHK(d, hipMemcpyAsync(h, d->mom_out, sizeof h, hipMemcpyDeviceToHost, d->stream));
   HIPCHK(d, hipStreamSynchronize(d->stream));
@@ -1323,11 +1320,12 @@ rwmi_status rwmi_read_moments(rwmi_domain* d, rwmi_moments* out) {
   return RWMI_OK;
 }
 
-// Same kernels and reduction order as rwmi_read_moments, with every buffer
-// they need (output staging [0, 32), reference point [32, 36), walker
-// partials from 64, node partials after them) in the library's per-GPU
-// scratch array.  Nothing there has to start at zero: each reduction block
-// writes its own partials and the final kernel writes every output word.
+// Same kernels as rwmi_read_moments, with every buffer they need (output
+// staging [0, 32), walker partials from 40, node partials after them) in the
+// library's per-GPU scratch array: the walker partials take at most 24 words
+// more than the 6 per 4096 walkers of the stated limit (18 per 16384).
+// Nothing there has to start at zero: each reduction block writes its own
+// partials and the final kernel writes every output word.
 rwmi_status rwmi_read_moments_noalloc(rwmi_domain* d, rwmi_moments* out) {
   if (!d || !out) return fail(d, RWMI_EINVAL, "null argument");
   if (!d->particles_uploaded && !d->parts.empty())
@@ -1344,11 +1342,9 @@ rwmi_status rwmi_read_moments_noalloc(rwmi_domain* d, rwmi_moments* out) {
   double* sc = nullptr;
   HIPCHK(d, rwmi::noalloc_scratch(&sc));
   double* outd = sc;
-  double* refd = sc + 32;
-  double* pw = sc + 64;
-  double* pn = pw + 6 * nbw;
-  HIPCHK(d, hipMemcpyAsync(refd, d->ref, 24, hipMemcpyHostToDevice, d->stream));
-  HIPCHK(d, rwmi::launch_moments(d->prec, d->dv, 0, N, nw, refd, pw, pn, outd, d->stream));
+  double* pw = sc + 40;
+  double* pn = pw + rwmi::moment_walker_words(nw);
+  HIPCHK(d, rwmi::launch_moments(d->prec, d->dv, 0, N, nw, d->ref, pw, pn, outd, d->stream));
   double h[32];
   HIPCHK(d, hipMemcpyAsync(h, outd, sizeof h, hipMemcpyDeviceToHost, d->stream));
   HIPCHK(d, hipStreamSynchronize(d->stream));

@@ -145,20 +145,36 @@ hipError_t launch_profile(const DomView* v, int dom, int axis, int n_layers, int
   return hipGetLastError();
 }
 
-hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double* ref, double* pw,
+// Chunks below which a block has 1024 threads, us with 1024 and with 256: 8
+// chunks (32^3 FP64) 18.8, 31.5; 125 (80^3) 18.7, 40.3; 512 (128^3) 36.0, 44.7;
+// 1728 (192^3) 73.6, 70.5; 4096 (256^3) 190, 127.
+constexpr int64_t kMomWideChunks = 1024;
+
+template <typename U>
+static void mom_nodes(bool wide, unsigned nbn, const DomView* v, int dom, double* pn, hipStream_t s) {
+  if (wide) k_mom_nodes<U, 1024><<<nbn, 1024, 0, s>>>(v, dom, pn);
+  else k_mom_nodes<U, 256><<<nbn, 256, 0, s>>>(v, dom, pn);
+}
+
+hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double ref[3], double* pw,
                           double* pn, double* out, hipStream_t s) {
-  const int64_t nbw = (nw + kRedChunk - 1) / kRedChunk;
+  const int64_t nbw = moment_walker_blocks(nw);
   const int64_t nbn = (N + kRedChunk - 1) / kRedChunk;
+  const MomRef r{{ref[0], ref[1], ref[2]}};
+  long long* iw = (long long*)pw;
   if (nbw > 0) {
-    k_ids_inverse<<<(unsigned)((nw + 255) / 256), 256, 0, s>>>(v, dom);
-    if (prec == P64) k_mom_walkers<double><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, ref, pw);
-    else k_mom_walkers<float><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, ref, pw);
+    if (prec == P64) k_mom_walkers<double><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, r, iw);
+    else k_mom_walkers<float><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, r, iw);
   }
-  if (prec == P64) k_mom_nodes<double><<<(unsigned)nbn, kRedThreads, 0, s>>>(v, dom, pn);
-  else k_mom_nodes<float><<<(unsigned)nbn, kRedThreads, 0, s>>>(v, dom, pn);
-  k_mom_final<<<1, 64, 0, s>>>(v, dom, pw, nbw, pn, nbn, out);
+  const bool wide = nbn < kMomWideChunks;
+  if (prec == P64) mom_nodes<double>(wide, (unsigned)nbn, v, dom, pn, s);
+  else mom_nodes<float>(wide, (unsigned)nbn, v, dom, pn, s);
+  k_mom_final<<<1, kRedThreads, 0, s>>>(v, dom, iw, nbw, pn, nbn, out);
   return hipGetLastError();
 }
+
+int64_t moment_walker_blocks(int64_t nw) { return (nw + kWalkChunk - 1) / kWalkChunk; }
+int64_t moment_walker_words(int64_t nw) { return kWalkWords * moment_walker_blocks(nw); }
 
 hipError_t launch_sort(int prec, const DomView* views, int dom, int64_t nw, const SortScratch& sc, hipStream_t s) {
   if (nw <= 0) return hipSuccess;

@@ -46,8 +46,11 @@ hipError_t launch_occupancy(const DomView* v, int dom, uint32_t* occ, int64_t N,
 // walkers per layer along `axis` (n_layers = n[axis] counts, cleared first)
 hipError_t launch_profile(const DomView* v, int dom, int axis, int n_layers, int64_t nw, uint32_t* counts,
                           hipStream_t s);
-// partial buffers: walkers ceil(nw/4096)*6, nodes ceil(N/4096)*12 doubles
-hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double* ref,
+// partial buffers: walkers moment_walker_words(nw) (18 per 16384), nodes
+// ceil(N/4096)*12 words of 8 bytes; ref: the walkers' reference point (host)
+int64_t moment_walker_blocks(int64_t nw);
+int64_t moment_walker_words(int64_t nw);
+hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double ref[3],
                           double* pw, double* pn, double* out, hipStream_t s);
 hipError_t launch_advance(const DomView* views, int nd, uint32_t n, hipStream_t s);
 // Two-way coupled particles of domain views[0] (dem_args: a device DemArgs,
