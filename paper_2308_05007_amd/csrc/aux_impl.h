@@ -430,10 +430,14 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_final(const DomView* __rest
   }
 }
 
-// End of a launch group: every domain of the launch has completed n more steps.
-__global__ void k_advance(const DomView* __restrict__ views, int nd_count, uint32_t n) {
+// End of a launch group: every domain of the launch has completed n more
+// steps, and swapped its two lattices (if it has two) `swaps` times.
+__global__ void k_advance(const DomView* __restrict__ views, int nd_count, uint32_t n, uint32_t swaps) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nd_count) views[i].tstep[0] += n;
+  if (i < nd_count) {
+    views[i].tstep[0] += n;
+    views[i].tstep[1] += swaps;
+  }
 }
 
 __global__ void k_normals(uint32_t k0, uint32_t k1, uint32_t t, uint32_t purpose, int64_t n, double* __restrict__ z) {

@@ -390,6 +390,23 @@ int launch_flags(const rwmi_domain* d) {
   return d->flags | (d->hv.ibb ? rwmi::kFlagIbb | rwmi::kFlagDensity : 0);
 }
 
+// Fluid steps in pairs (pair_impl.h)?  The byte offsets of the lattice and the
+// velocities have to fit 32 bits, and the pass has to be the faster one: a
+// block plane takes some 5.3 us where rows begin at 64-byte sectors and 6.5
+// where they do not, a single step 30.6 ps per node.  us per fluid step, single
+// and paired: 256^3 512, 332; 250^3 484, 404; 224^3 348, 271; 192^3 219, 163;
+// 176^3 170, 143; 1000x120x120 445, 330; and refused 219x187x241 305, 318;
+// 171x193x165 171, 185 (with 20 particles).  Walkers run 45 us per 1e7 slower
+// apart from the fluid, which two walkers per node make as much as a pair gains.
+bool pair_steps(const rwmi_domain* d, rwmi::PairArgs& a) {
+  const DomView& v = d->hv;
+  if (v.inplace || v.ibb || d->dem || d->prec != RWMI_FP32 || v.bc[0] || v.bc[1] || v.bc[2]) return false;
+  if (rwmi::f_elems(v.N) > (1ull << 30) || v.nw > 2 * v.N) return false;
+  a = rwmi::pair_shape(v.n[0], v.n[1], v.n[2]);
+  const double plane_us = v.n[0] % 16 == 0 ? 5.3 : 6.5;
+  return 0.5 * plane_us * (double)a.cost < 0.92 * 30.6e-6 * (double)v.N;
+}
+
 rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturing) {
   if (d->dem) return enqueue_group_dem(d, n, record, capturing);
   int b[kRoles];
@@ -403,6 +420,29 @@ rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturin
     d->evrec.push_back({win.ev, win.launches, win.fluid, win.walkers});
     open = false;
     return RWMI_OK;
+  };
+  // Steps taken in pairs: the fluid updates of t0 + j and t0 + j + 1 (j even)
+  // are one launch of their own after launch j, which has brought the poses of
+  // the second and moved the walkers whose velocities it overwrites; launches j
+  // and j + 1 carry no fluid.  The last step of an odd n is an ordinary one.
+  rwmi::PairArgs pa{};
+  const bool pairs = pair_steps(d, pa);
+  uint32_t swaps = 0;
+  auto begin = [&](bool timed) -> rwmi_status {
+    if (!timed || open) return RWMI_OK;
+    win = TimedWindowState{d->evused, 0, 0, 0};
+    hipEvent_t e0 = take_event(d), e1 = take_event(d);
+    if (!e0 || !e1) return fail(d, RWMI_EDEVICE, "hipEventCreate failed");
+    HIPCHK(d, hipEventRecord(e0, A));
+    open = true;
+    return RWMI_OK;
+  };
+  auto count = [&](bool timed, uint32_t fluid, uint32_t walkers) -> rwmi_status {
+    if (!timed) return RWMI_OK;
+    win.launches += 1;
+    win.fluid += fluid;
+    win.walkers += walkers;
+    return win.launches >= d->timing_every ? close_window() : RWMI_OK;
   };
   for (int j = -1; j <= (int)n; ++j) {
     if (j >= 0 && sort_before(d, (uint32_t)j, n, capturing)) {
@@ -419,27 +459,31 @@ rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturin
     a.flags = launch_flags(d) | (j == (int)n - 1 ? rwmi::kFlagDensity : 0);
     a.inplace = d->hv.inplace;
     a.j = j;
-    if (a.nb[0] + a.nb[1] + a.nb[2] == 0) continue;
+    a.s = (int32_t)swaps;
+    const bool paired = pairs && j >= 0 && (j | 1) < (int)n;
+    if (paired) a.nb[kRoleFluid] = 0;
     const bool timed = record && j >= 0;
-    if (timed && !open) {
-      win = TimedWindowState{d->evused, 0, 0, 0};
-      hipEvent_t e0 = take_event(d), e1 = take_event(d);
-      if (!e0 || !e1) return fail(d, RWMI_EDEVICE, "hipEventCreate failed");
-      HIPCHK(d, hipEventRecord(e0, A));
-      open = true;
+    if (a.nb[0] + a.nb[1] + a.nb[2] > 0) {
+      if (begin(timed) != RWMI_OK) return RWMI_EDEVICE;
+      if (d->hv.ibb && a.nb[kRoleFluid] > 0)
+        HIPCHK(d, rwmi::launch_ibb_links(d->prec, d->dv, 0, j, false, (unsigned)a.nb[kRoleFluid], A));
+      HIPCHK(d, rwmi::launch_step(d->prec, d->bs, a, A));
+      if (a.nb[kRoleFluid] > 0) ++swaps;
+      if (count(timed, a.nb[kRoleFluid] > 0, a.nb[kRoleWalk] > 0) != RWMI_OK) return RWMI_EDEVICE;
     }
-    if (d->hv.ibb && a.nb[kRoleFluid] > 0)
-      HIPCHK(d, rwmi::launch_ibb_links(d->prec, d->dv, 0, j, false, (unsigned)a.nb[kRoleFluid], A));
-    HIPCHK(d, rwmi::launch_step(d->prec, d->bs, a, A));
-    if (timed) {
-      win.launches += 1;
-      win.fluid += a.nb[kRoleFluid] > 0 ? 1u : 0u;
-      win.walkers += a.nb[kRoleWalk] > 0 ? 1u : 0u;
-      if (win.launches == d->timing_every && close_window() != RWMI_OK) return RWMI_EDEVICE;
+    if (paired && (j & 1) == 0) {
+      pa.j = j;
+      pa.s = (int32_t)swaps;
+      pa.dens = j + 2 == (int)n;
+      if (begin(timed) != RWMI_OK) return RWMI_EDEVICE;
+      HIPCHK(d, rwmi::launch_pair(d->hv.has_force != 0, (int64_t)d->hv.n[0] * d->hv.n[1] % rwmi::kTile == 0, pa,
+                                   d->dv, A));
+      ++swaps;
+      if (count(timed, 2, 0) != RWMI_OK) return RWMI_EDEVICE;
     }
   }
   if (close_window() != RWMI_OK) return RWMI_EDEVICE;
-  HIPCHK(d, rwmi::launch_advance(d->dv, 1, n, A));
+  HIPCHK(d, rwmi::launch_advance(d->dv, 1, n, swaps, A));
   return RWMI_OK;
 }
 
@@ -484,7 +528,7 @@ rwmi_status enqueue_group_dem(rwmi_domain* d, uint32_t n, bool record, bool capt
     a.nb[kRoleFluid] = j < (int)n ? b[kRoleFluid] : 0;
     a.flags = launch_flags(d) | rwmi::kFlagDem | (j == (int)n - 1 ? rwmi::kFlagDensity : 0);
     a.inplace = d->hv.inplace;
-    a.j = j;
+    a.j = a.s = j;
     if (a.nb[kRoleWalk] + a.nb[kRoleFluid] > 0) {
       if (open() != RWMI_OK) return RWMI_EDEVICE;
       if (d->hv.ibb && a.nb[kRoleFluid] > 0)
@@ -508,7 +552,7 @@ rwmi_status enqueue_group_dem(rwmi_domain* d, uint32_t n, bool record, bool capt
     if (close() != RWMI_OK) return RWMI_EDEVICE;
     if (record) d->evdem.push_back({ev, 2});
   }
-  HIPCHK(d, rwmi::launch_advance(d->dv, 1, n, A));
+  HIPCHK(d, rwmi::launch_advance(d->dv, 1, n, n, A));
   return RWMI_OK;
 }
 
@@ -1784,13 +1828,13 @@ static rwmi_status batch_enqueue_group(rwmi_batch* b, uint32_t n, bool capturing
       launch_roles(g.blocks, j, n, a.nb);
       a.flags = b->flags | (j == (int)n - 1 ? rwmi::kFlagDensity : 0);
       a.inplace = g.inplace;
-      a.j = j;
+      a.j = a.s = j;
       if (a.nb[0] + a.nb[1] + a.nb[2] == 0) continue;
       if (rwmi::launch_step(g.prec, g.bs, a, A) != hipSuccess) return bfail(b, RWMI_EDEVICE, "batch launch failed");
     }
   }
   for (auto& g : b->groups)
-    if (rwmi::launch_advance(g.views, (int)g.doms.size(), n, A) != hipSuccess)
+    if (rwmi::launch_advance(g.views, (int)g.doms.size(), n, n, A) != hipSuccess)
       return bfail(b, RWMI_EDEVICE, "batch advance failed");
   return RWMI_OK;
 }

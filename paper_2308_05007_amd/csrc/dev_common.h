@@ -161,8 +161,8 @@ struct DomView {
   float eF_f[kQ];                 // e_i . F per direction (float collision)
   double wu[3][2][3];             // wall velocity [axis][lo/hi][component]
   float wu_f[3][2][3];
-  void* fA;                       // distributions (fidx): parity 0 source (two lattices) or the lattice (in place)
-  void* fB;                       // distributions, parity 1 source (two lattices only)
+  void* fA;                       // distributions (fidx): one of two lattices, or the lattice (in place)
+  void* fB;                       // distributions, the other lattice (two lattices only)
   void* u[2];                     // (ux, uy, uz) per node (3 U), written by step t into [t & 1]
   void* rho;                      // density per node, written by the last fluid step of a group
   const DevParticle* parts;
@@ -175,7 +175,8 @@ struct DomView {
                                   // at t and t+1
   float* sph[3];                  // per step t, slot t mod 3: [np][4] walker filter spheres at
                                   // t+1: centre, (rb + 1/2 + kSphereMargin)^2
-  uint64_t* tstep;                // [0] steps completed before the current launch group
+  uint64_t* tstep;                // before the current launch group: [0] steps completed,
+                                  // [1] swaps of the two lattices (odd: fB holds f*)
   unsigned long long* mask[3];    // per step t, slot t mod 3: coarse cull mask at P(t+1)
   unsigned long long* fcull[3];   // per step t, slot t mod 3: bit p set when particle p's
                                   // solid-fraction support at P(t) meets fluid block b
@@ -203,6 +204,12 @@ struct DomView {
 template <typename T>
 __device__ __forceinline__ __attribute__((address_space(1))) T* gp(T* p) {
   return (__attribute__((address_space(1))) T*)p;
+}
+
+// Address of a wave-uniform base plus a 32-bit byte offset per lane.
+template <typename T, typename BP>
+__device__ __forceinline__ __attribute__((address_space(1))) T* at_byte(BP base, uint32_t off) {
+  return (__attribute__((address_space(1))) T*)((__attribute__((address_space(1))) char*)base + (size_t)off);
 }
 
 // Block barrier that orders LDS only: global memory operations in flight

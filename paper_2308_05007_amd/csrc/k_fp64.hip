@@ -210,8 +210,8 @@ hipError_t launch_ids_identity(const DomView* views, int dom, int64_t nw, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_advance(const DomView* views, int nd, uint32_t n, hipStream_t s) {
-  k_advance<<<(nd + 63) / 64, 64, 0, s>>>(views, nd, n);
+hipError_t launch_advance(const DomView* views, int nd, uint32_t n, uint32_t swaps, hipStream_t s) {
+  k_advance<<<(nd + 63) / 64, 64, 0, s>>>(views, nd, n, swaps);
   return hipGetLastError();
 }
 

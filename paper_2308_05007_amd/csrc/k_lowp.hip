@@ -1,9 +1,19 @@
 // FP32 / FP16-storage / BF16-storage kernels (collision and walker
 // arithmetic in float; contraction to FMA allowed).
 #include "launch.h"
+#include "pair_impl.h"
 #include "step_impl.h"
 
 namespace rwmi {
+
+// walkers are float in every storage mode
+static void walk_bs(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
+  switch (bs) {
+    case 128: k_walk<P32, 128><<<g, 128, 0, s>>>(a, a.views, a.boff); break;
+    case 512: k_walk<P32, 512><<<g, 512, 0, s>>>(a, a.views, a.boff); break;
+    default: k_walk<P32, 256><<<g, 256, 0, s>>>(a, a.views, a.boff); break;
+  }
+}
 
 template <int P, bool IP>
 static void step_bs(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
@@ -16,6 +26,10 @@ static void step_bs(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
 
 template <int P>
 static void step_layout(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
+  if (a.nb[kRoleFluid] == 0) {  // walkers and prologue only
+    walk_bs(bs, g, a, s);
+    return;
+  }
   if (a.flags & kFlagIbb) {  // bounce-back coupling: two lattices, 256 threads per block; the link
                              // pass carries the coupled particles' momentum exchange
     k_step<P, 256, false, false, true><<<g, 256, 0, s>>>(a, a.views, a.boff);
@@ -52,6 +66,15 @@ hipError_t launch_ibb_links_lowp(int prec, const DomView* v, int dom, int32_t j,
   if (prec == P32) links<P32>(v, dom, j, dem, blocks, s);
   else if (prec == P16) links<P16>(v, dom, j, dem, blocks, s);
   else links<PB16>(v, dom, j, dem, blocks, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_pair(bool force, bool aligned, const PairArgs& a, const DomView* v, hipStream_t s) {
+  const unsigned g = 8u * (unsigned)xcd_count(a.ntx * a.nty * a.nzc, 0);
+  if (force && aligned) k_pair<true, true><<<g, kPairThreads, 0, s>>>(a, v);
+  else if (force) k_pair<true, false><<<g, kPairThreads, 0, s>>>(a, v);
+  else if (aligned) k_pair<false, true><<<g, kPairThreads, 0, s>>>(a, v);
+  else k_pair<false, false><<<g, kPairThreads, 0, s>>>(a, v);
   return hipGetLastError();
 }
 

@@ -52,7 +52,10 @@ int64_t moment_walker_blocks(int64_t nw);
 int64_t moment_walker_words(int64_t nw);
 hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double ref[3],
                           double* pw, double* pn, double* out, hipStream_t s);
-hipError_t launch_advance(const DomView* views, int nd, uint32_t n, hipStream_t s);
+hipError_t launch_advance(const DomView* views, int nd, uint32_t n, uint32_t swaps, hipStream_t s);
+// Two fluid steps of FP32 domain views[0] in one launch (pair_impl.h).  force:
+// the domain has a body force; aligned: nx ny is a multiple of kTile.
+hipError_t launch_pair(bool force, bool aligned, const PairArgs& a, const DomView* views, hipStream_t s);
 // Two-way coupled particles of domain views[0] (dem_args: a device DemArgs,
 // dem_impl.h): the particle update of step tstep + j, and the pose tables of
 // step tstep from the particle state.

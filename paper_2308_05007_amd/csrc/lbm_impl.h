@@ -658,19 +658,18 @@ __global__ void __launch_bounds__(256) k_ibb_links(const DomView* __restrict__ v
 // go into the block's accumulator dacc ([64][6], LDS) in fixed point, so
 // that the sums do not depend on the order of the nodes.
 template <int P, int BS, int L, bool DEM, bool IBB>
-__device__ __forceinline__ void fluid_node(const DomView& V, uint32_t lb, uint64_t t, bool nt, bool dens,
+__device__ __forceinline__ void fluid_node(const DomView& V, uint32_t lb, uint64_t t, bool lat, bool nt, bool dens,
                                            unsigned long long* dacc) {
   using S = typename Store<P>::S;
   using R = typename Store<P>::C;
   constexpr bool exact = (P == P64);
   using SR = typename Raw<S>::T;
-  // two lattices: read the parity-t buffer, write the other; in place (one
+  // two lattices: read fA (lat: fB), write the other; in place (one
   // lattice): every access goes to fA, the slots depending on t's parity
   constexpr bool inplace = L != kTwoLattices;
   constexpr bool odd_ip = L == kInPlaceOdd;
-  const bool odd = (t & 1ull) != 0;
-  const auto src = gp((const SR*)((inplace || !odd) ? V.fA : V.fB));
-  SR* dst0 = (SR*)((inplace || odd) ? V.fA : V.fB);
+  const auto src = gp((const SR*)((inplace || !lat) ? V.fA : V.fB));
+  SR* dst0 = (SR*)((inplace || lat) ? V.fA : V.fB);
   // In place, dst equals src; hide that from the optimiser, which would
   // otherwise keep all 19 load addresses live until the stores instead of
   // recomputing them (this only moves a register value, no memory access).
@@ -1099,15 +1098,15 @@ __device__ __forceinline__ void fluid_node(const DomView& V, uint32_t lb, uint64
 // momentum at its links only, in the link pass: its fluid blocks take the
 // non-DEM form.
 template <int P, int BS, int L, bool DEM, bool IBB = false>
-__device__ __forceinline__ void fluid_block(const DomView& V, uint32_t lb, uint64_t t, bool nt, bool dens,
+__device__ __forceinline__ void fluid_block(const DomView& V, uint32_t lb, uint64_t t, bool lat, bool nt, bool dens,
                                             unsigned long long* dacc) {
   static_assert(!(DEM && IBB), "bounce-back links carry the momentum exchange");
   if constexpr (!DEM) {
-    fluid_node<P, BS, L, false, IBB>(V, lb, t, nt, dens, dacc);
+    fluid_node<P, BS, L, false, IBB>(V, lb, t, lat, nt, dens, dacc);
   } else {
     for (int k = threadIdx.x; k < 6 * kMaxParticles; k += BS) dacc[k] = 0ull;
     lds_barrier();
-    fluid_node<P, BS, L, true, IBB>(V, lb, t, nt, dens, dacc);
+    fluid_node<P, BS, L, true, IBB>(V, lb, t, lat, nt, dens, dacc);
     lds_barrier();
     // the block's sums into the step's accumulator (two's-complement adds:
     // exact, in any order)
@@ -1178,7 +1177,7 @@ __global__ void k_read_f(const DomView* __restrict__ views, int dom, double* __r
   if (id >= V.N) return;
   const uint64_t t = V.tstep[0];  // steps completed: the gather of step t
   const bool inplace = V.inplace != 0, odd = (t & 1ull) != 0;
-  const S* src = (const S*)((!inplace && odd) ? V.fB : V.fA);
+  const S* src = (const S*)((!inplace && (V.tstep[1] & 1ull)) ? V.fB : V.fA);
   const int nx = V.n[0], ny = V.n[1], nz = V.n[2];
   const int nd[3] = {(int)(id % nx), (int)((id / nx) % ny), (int)(id / ((int64_t)nx * ny))};
   for (int a = 0; a < 3; ++a)

@@ -45,6 +45,31 @@ constexpr int step_waves_per_eu() {
   return P == P64 ? 1 : (P == P32 ? RWMI_STEP_WAVES_PER_EU_32 : RWMI_STEP_WAVES_PER_EU_16);
 }
 
+// A launch without fluid blocks (steps taken in pairs, the coupled particles'
+// prologue, the ends of a group): walker and prologue blocks in the registers
+// those take.
+#ifndef RWMI_WALK_WAVES
+#define RWMI_WALK_WAVES 8
+#endif
+template <int P, int BS>
+__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(P == P64 ? 1 : RWMI_WALK_WAVES)))
+k_walk(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict__ boff) {
+  __shared__ union {
+    WalkLds<typename Store<P>::O, BS> walk;
+    ProLds pro;
+  } lds;
+  int idx = 0;
+  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & 1) != 0, idx);
+  if (role == kRoleNone) return;
+  const int32_t* bo = boff + role * (a.nd + 1);
+  const int d = find_domain(bo, a.nd, idx);
+  const DomView& V = views[d];
+  const int lb = idx - bo[d];
+  const uint64_t t = step_of(V, a.j);
+  if (role == kRoleWalk) walk_block<P, BS>(V, lb, t - 1, lds.walk);
+  else prologue_block(V, lb, t + 1, BS, lds.pro, (a.flags & kFlagDem) != 0);
+}
+
 // DEM: the launch's domains have two-way coupled particles (the fluid
 // blocks accumulate the hydrodynamic force and torque on them).  IBB: they
 // couple fluid and particles by interpolated bounce-back (two lattices).
@@ -66,9 +91,14 @@ k_step(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict_
   else if (role == kRolePro) prologue_block(V, lb, t + 1, BS, lds.pro, (a.flags & kFlagDem) != 0);
   else {
     const bool nt = (a.flags & kFlagNontemporal) != 0, dens = (a.flags & kFlagDensity) != 0;
-    if constexpr (!IP) fluid_block<P, BS, kTwoLattices, DEM, IBB>(V, (uint32_t)lb, t, nt, dens, lds.dem);
-    else if (t & 1ull) fluid_block<P, BS, kInPlaceOdd, DEM>(V, (uint32_t)lb, t, nt, dens, lds.dem);
-    else fluid_block<P, BS, kInPlaceEven, DEM>(V, (uint32_t)lb, t, nt, dens, lds.dem);
+    if constexpr (!IP) {
+      const bool lat = ((kp(V.tstep)[1] + (uint64_t)a.s) & 1ull) != 0;
+      fluid_block<P, BS, kTwoLattices, DEM, IBB>(V, (uint32_t)lb, t, lat, nt, dens, lds.dem);
+    } else if (t & 1ull) {
+      fluid_block<P, BS, kInPlaceOdd, DEM>(V, (uint32_t)lb, t, false, nt, dens, lds.dem);
+    } else {
+      fluid_block<P, BS, kInPlaceEven, DEM>(V, (uint32_t)lb, t, false, nt, dens, lds.dem);
+    }
   }
 }
 

@@ -63,7 +63,46 @@ struct StepArgs {
   int flags;            // kFlagXcd | kFlagNontemporal | kFlagDensity
   int inplace;          // every domain of the launch streams its lattice in place
   int32_t j;            // launch index within the group (-1: the prologue-only launch)
+  int32_t s;            // lattice swaps of the group before this launch (two lattices)
 };
+
+// One launch of two fluid steps (pair_impl.h): tiles of tx x ty nodes (the last
+// of a row or column may be smaller), ntx x nty of them, each in nzc runs of
+// planes.
+constexpr int kPairTx = 64, kPairTy = 8;
+constexpr int kPairRim = (kPairTx + 2) * (kPairTy + 2);  // nodes of a tile and its rim
+constexpr int kPairThreads = 704;                        // whole waves
+static_assert(kPairRim <= kPairThreads, "a thread per node");
+struct PairArgs {
+  int tx, ty, ntx, nty, nzc;
+  int dens;   // store the densities of the second step
+  int32_t j;  // the first step's offset within the group
+  int32_t s;  // lattice swaps of the group before this launch
+  int64_t cost;  // pair_shape's
+};
+
+// Tiles and runs of planes of an nx x ny x nz lattice: whole tiles (rows of 64
+// floats, so that they begin where lines do; the last of a row or column is
+// what is left), and the number of runs whose blocks fill the last round of the
+// chip best (256 CUs, one block each; a run of m planes walks m + 2).
+// cost: block planes walked one after the other on a CU.
+inline PairArgs pair_shape(int nx, int ny, int nz) {
+  PairArgs a{};
+  a.tx = nx < kPairTx ? nx : kPairTx;
+  a.ty = ny < kPairTy ? ny : kPairTy;
+  a.ntx = (nx + a.tx - 1) / a.tx;
+  a.nty = (ny + a.ty - 1) / a.ty;
+  a.cost = -1;
+  for (int c = 1; c <= (nz + 3) / 4; ++c) {
+    const int64_t rounds = ((int64_t)a.ntx * a.nty * c + 255) / 256;
+    const int64_t cost = rounds * ((nz + c - 1) / c + 2);
+    if (a.cost < 0 || cost < a.cost) {
+      a.cost = cost;
+      a.nzc = c;
+    }
+  }
+  return a;
+}
 
 // Share of XCD x of n items dealt in contiguous runs: count and first item.
 RWMI_HD inline int xcd_count(int n, int x) { return (n >> 3) + (x < (n & 7) ? 1 : 0); }
