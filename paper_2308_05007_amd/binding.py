@@ -424,7 +424,7 @@ class Domain:
         img = np.empty(max(3 * m, 1), np.int32)
         vp = lambda a: a.ctypes.data_as(C.c_void_p)
         self._ck(self.L.rwmi_read_walkers(self.h, vp(cell), vp(off), vp(img)))
-        return cell[:m].copy(), off[:3 * m].reshape(3, m).copy(), img[:3 * m].reshape(3, m).copy()
+        return cell[:m], off[:3 * m].reshape(3, m), img[:3 * m].reshape(3, m)
 
     def distributions(self):
         f = np.empty(19 * self.N)

@@ -635,12 +635,28 @@ __global__ void k_ids_identity(const DomView* __restrict__ views, int dom) {
   gp(V.wid)[w] = (int32_t)w;
 }
 
-// The id -> slot map, built when a read-out needs walkers in id order.
-__global__ void k_ids_inverse(const DomView* __restrict__ views, int dom) {
+// The walkers in id order, for a read-out, in the sort's scratch (free between
+// launches, so that a read-out allocates nothing on the device).  An id out of
+// range (a corrupt map) sets *bad, which starts at zero.  Scattered by one host
+// thread they took 23 of the 25 ms of a read-out of 1e6 walkers.
+template <typename R>
+__global__ void __launch_bounds__(256) k_read_walkers(const DomView* __restrict__ views, int dom,
+                                                      int32_t* __restrict__ cell, R* __restrict__ off,
+                                                      int32_t* __restrict__ img, uint32_t* __restrict__ bad) {
   const DomView& V = views[dom];
-  const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= V.nw) return;
-  gp(V.winv)[gp(V.wid)[w]] = (int32_t)w;
+  const int64_t nw = V.nw, w = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (w >= nw) return;
+  const uint32_t id = (uint32_t)gp(V.wid)[w];
+  if (id >= (uint64_t)nw) {
+    gp(bad)[0] = 1u;
+    return;
+  }
+  gp(cell)[id] = gp(V.wcell)[w];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    gp(off)[a * nw + id] = gp((const R*)V.woff)[a * nw + w];
+    gp(img)[a * nw + id] = gp(V.wimg)[a * nw + w];
+  }
 }
 
 }  // namespace rwmi

@@ -210,6 +210,15 @@ hipError_t launch_ids_identity(const DomView* views, int dom, int64_t nw, hipStr
   return hipGetLastError();
 }
 
+hipError_t launch_read_walkers(int prec, const DomView* v, int dom, int64_t nw, const SortScratch& sc,
+                               hipStream_t s) {
+  const unsigned g = (unsigned)((nw + 255) / 256);
+  k_fill_u32<<<1, 256, 0, s>>>(sc.bin, 1, 0u);
+  if (prec == P64) k_read_walkers<double><<<g, 256, 0, s>>>(v, dom, sc.cell, (double*)sc.off, sc.img, sc.bin);
+  else k_read_walkers<float><<<g, 256, 0, s>>>(v, dom, sc.cell, (float*)sc.off, sc.img, sc.bin);
+  return hipGetLastError();
+}
+
 hipError_t launch_advance(const DomView* views, int nd, uint32_t n, uint32_t swaps, hipStream_t s) {
   k_advance<<<(nd + 63) / 64, 64, 0, s>>>(views, nd, n, swaps);
   return hipGetLastError();

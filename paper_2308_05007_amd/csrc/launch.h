@@ -82,6 +82,10 @@ struct SortScratch {
 };
 // Regroup the walkers of domain `dom` of `views` by coarse mask block.
 hipError_t launch_sort(int prec, const DomView* views, int dom, int64_t nw, const SortScratch& sc, hipStream_t s);
+// Walkers in id order into sc.cell, sc.off and sc.img; sc.bin[0] nonzero: the
+// slots' ids are corrupt.
+hipError_t launch_read_walkers(int prec, const DomView* views, int dom, int64_t nw, const SortScratch& sc,
+                               hipStream_t s);
 // Slot i holds walker i (after seeding).
 hipError_t launch_ids_identity(const DomView* views, int dom, int64_t nw, hipStream_t s);
 hipError_t launch_normals(uint64_t seed, uint32_t t, uint32_t purpose, int64_t n, double* z, hipStream_t s);
