@@ -844,9 +844,9 @@ uint64_t rwmi_footprint_bytes(const rwmi_domain_desc* s, uint32_t n_particles, u
   b += sizeof(DomView) + 64 + 16;
   b += n_particles * sizeof(DevParticle) + 48 * n_ctrl_total + (288 + 48) * n_particles +
        (n_particles ? 24 * nmb + 24 * (uint64_t)fcull_words((int64_t)N) : 0);
-  // walkers: cell, offsets, images, id and slot maps; sort scratch (bin, rank
+  // walkers: cell, offsets, images, ids; sort scratch (bin, rank
   // and a second copy of the walker record) and the bin counts
-  b += n_walkers * (4 + 3 * off_size(p) + 12 + 8);
+  b += n_walkers * (4 + 3 * off_size(p) + 12 + 4);
   b += n_walkers * (8 + 4 + 3 * off_size(p) + 12 + 4) + 68 * nmb + 4 * (nmb / 4096 + 1);
   b += 4 * N;  // occupancy
   b += 8 * (6 * ((n_walkers + 4095) / 4096) + 12 * ((N + 4095) / 4096) + 64);
@@ -1070,14 +1070,14 @@ rwmi_status rwmi_seed_walkers(rwmi_domain* d, const rwmi_seed_desc* s, uint64_t 
     m += hflag[w];
   }
   // walker arrays of the final size
-  int32_t *wcell, *wimg, *wid, *winv;
+  int32_t *wcell, *wimg, *wid;
   void* woff;
   const int64_t m1 = std::max<int64_t>(m, 1);
   rwmi::SortScratch& sc = d->sort;
   sc.nbins = (int64_t)d->hv.mb[0] * d->hv.mb[1] * d->hv.mb[2];
   if ((st = alloc_into(d, wcell, 4 * m1)) != RWMI_OK || (st = alloc_into(d, woff, 3 * osz * m1)) != RWMI_OK ||
       (st = alloc_into(d, wimg, 12 * m1)) != RWMI_OK || (st = alloc_into(d, wid, 4 * m1)) != RWMI_OK ||
-      (st = alloc_into(d, winv, 4 * m1)) != RWMI_OK || (st = alloc_into(d, sc.hist, 68 * sc.nbins + 4 * (sc.nbins / 4096 + 1))) != RWMI_OK ||
+      (st = alloc_into(d, sc.hist, 68 * sc.nbins + 4 * (sc.nbins / 4096 + 1))) != RWMI_OK ||
       (st = alloc_into(d, sc.bin, 4 * m1)) != RWMI_OK || (st = alloc_into(d, sc.rank, 4 * m1)) != RWMI_OK ||
       (st = alloc_into(d, sc.cell, 4 * m1)) != RWMI_OK || (st = alloc_into(d, sc.off, 3 * osz * m1)) != RWMI_OK ||
       (st = alloc_into(d, sc.img, 12 * m1)) != RWMI_OK || (st = alloc_into(d, sc.wid, 4 * m1)) != RWMI_OK)
@@ -1086,7 +1086,6 @@ rwmi_status rwmi_seed_walkers(rwmi_domain* d, const rwmi_seed_desc* s, uint64_t 
   d->hv.woff = woff;
   d->hv.wimg = wimg;
   d->hv.wid = wid;
-  d->hv.winv = winv;
   d->hv.nw = m;
   if ((st = upload_view(d)) != RWMI_OK) return cleanup(), st;
   if (m > 0) {

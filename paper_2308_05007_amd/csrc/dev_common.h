@@ -184,7 +184,6 @@ struct DomView {
   void* woff;                     // walker offsets SoA [3][nw] (double or float)
   int32_t* wimg;                  // walker image counts SoA [3][nw]
   int32_t* wid;                   // walker id held by slot i (Philox counter, read-back order)
-  int32_t* winv;                  // slot of walker id w (inverse of wid; built for read-outs)
   unsigned long long* counters;   // kCounters
   uint32_t* occ;                  // occupancy per node
   int32_t ibb;                    // interpolated bounce-back coupling instead of partially
