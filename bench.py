@@ -86,8 +86,8 @@ def kernel_source_hash(prec):
     """Hash of the sources the step kernel of this precision is built from."""
     h = hashlib.sha256()
     unit = "k_fp64.hip" if prec == "fp64" else "k_lowp.hip"
-    for f in ("step_impl.h", "step_map.h", "lbm_impl.h", "walk_impl.h", "pro_impl.h", "dev_common.h", "launch.h",
-              unit):
+    for f in ("step_impl.h", "step_map.h", "lbm_impl.h", "walk_impl.h", "pro_impl.h", "pair_impl.h", "dev_common.h",
+              "launch.h", unit):
         with open(os.path.join(ROOT, "paper_2308_05007_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -213,10 +213,19 @@ def measure(cfg, key, steps, warmup, timing, burnin=0):
     avg_s = ms_total / 1e3 / max(launches, 1)
     # a full launch carries one fluid update and one walker step
     fb, wb = fluid_nodes(cfg) * fluid_bytes_per_node(prec), nw * walker_bytes_per_step(prec)
+    # unless fluid updates are taken two per pass (three launches for two
+    # steps: each step's walkers and the pair), which reads and writes the
+    # distributions once for both
+    pairs = nw > 0 and launches > 1.25 * fluid_launches > 5
+    if pairs:
+        fb -= fluid_nodes(cfg) * 19 * ELEM[prec]
     achieved = (fluid_launches * fb + walker_launches * wb) / (ms_total / 1e3) / 1e9
     return {"key": key, "prec": prec, "N": N, "nw": nw, "dt": dt, "steps": steps, "burnin": burnin,
             "mlups": N * steps / dt / 1e6, "wsps": nw * steps / dt, "achieved": achieved,
-            "bytes_launch": fb + wb, "avg_us": avg_s * 1e6, "launches": launches, "mom": mom}
+            "bytes_launch": (fluid_launches * fb + walker_launches * wb) // max(launches, 1) if pairs else fb + wb,
+            "avg_us": avg_s * 1e6, "launches": launches, "mom": mom,
+            "kernel": "k_pair (two fluid updates per pass) and k_walk (walkers, particle prologue)" if pairs else
+                      "k_step (fused: PSM-BGK collide + pull-stream, walkers, particle prologue)"}
 
 
 def bench_plain(args):
@@ -257,7 +266,7 @@ def bench_plain(args):
                      "frac": round(r["achieved"] / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
                      "traffic_over_algorithmic": round(traffic / traffic_alg, 4) if traffic and traffic_alg else None,
-                     "kernel": "k_step (fused: PSM-BGK collide + pull-stream, walkers, particle prologue)",
+                     "kernel": r["kernel"],
                      "bytes_per_launch": r["bytes_launch"], "avg_launch_us": round(r["avg_us"], 2),
                      "timed_launches": r["launches"], "timing_window": args.timing_every},
         "counters": mom["counters"],

@@ -19,8 +19,10 @@
 // blocks per pass are chosen to fill whole rounds of the chip (pair_shape).
 //
 // Measured, us per fluid step, single and paired: 256^3 508 -> 294, 224^3 348 ->
-// 271, 192^3 219 -> 163.  The pass moves 1.05 times its own bytes at 5.1 TB/s
-// with rim reads included; tiles 32 x 16 352, 32 x 8 423, 64 x 12 342 at 256^3.
+// 271, 192^3 219 -> 163.  A pass moves 1.19 times its own bytes (the rims)
+// at 5.2 TB/s; tiles 32 x 16 352, 32 x 8 423, 64 x 12 342 at 256^3, and with 4,
+// 8 runs of planes (2, 4 rounds of blocks) instead of 2 the step with particles
+// and walkers 489, 504 instead of 464.
 // With 16-bit storage the bytes no longer bound it and it gained nothing (281
 // against 275).  The walkers then run in a launch of their own, 142 us per step
 // for 1e7 where beside the single step's fluid they add 95: the whole step at
