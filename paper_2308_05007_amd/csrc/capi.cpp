@@ -206,8 +206,8 @@ void release(rwmi_domain* d, void* p) {
 // deinterleaved, up to 8 MB through one host buffer.  Beyond that the caller's
 // pages are mostly new, and one thread writing them reaches 4-9 GB/s, eight
 // threads 60, the link 48 through pinned memory: chunks go through pinned
-// buffers of this call, one per worker, which brings a chunk to its buffer and
-// lays it out while the others' chunks are on the link.  Workers end with the
+// buffers of this call, one per worker, which waits for its chunk in its buffer
+// and lays it out while the others' chunks are on the link.  Workers end with the
 // call; without them (or pinned memory) the calling thread does it all.  Below
 // the limits starting them, and the first touch of the pinned pages, cost what
 // they gain (distributions of 48^3, 17 MB: 0.7-2.3 ms with them, 1.0 without;
@@ -319,6 +319,10 @@ rwmi_status copy_out(rwmi_domain* d, const Piece* pieces, int n) {
     chunks += chunks_of(i);
   }
   if (weight <= kDirectBytes) return copy_out_direct(d, pieces, n);
+  // What the pieces are made by has to be done before another thread copies
+  // them: d->stream may be hipStreamPerThread, which names a stream of its own
+  // in each worker.
+  HIPCHK(d, hipStreamSynchronize(d->stream));
   const int workers = (int)std::min<size_t>(kCopyWorkers, chunks);
   CopyBuffer buf(kCopyChunk * (size_t)workers, true);
   if (!buf.p) return fail(d, RWMI_ENOMEM, "host allocation of %zu bytes failed", kCopyChunk * (size_t)workers);
@@ -343,7 +347,10 @@ rwmi_status copy_out(rwmi_domain* d, const Piece* pieces, int n) {
       if (e == hipSuccess) c.deliver(mine, first, m);
     }
     if (ev) (void)hipEventDestroy(ev);
-    if (e != hipSuccess) error.store((int)e);
+    if (e != hipSuccess) {
+      error.store((int)e);
+      (void)hipStreamSynchronize(d->stream);  // before the buffers go
+    }
   };
   std::thread helpers[kCopyWorkers];
   try {
@@ -353,9 +360,7 @@ rwmi_status copy_out(rwmi_domain* d, const Piece* pieces, int n) {
   work(0);
   for (std::thread& t : helpers)
     if (t.joinable()) t.join();
-  const hipError_t sync = hipStreamSynchronize(d->stream);  // before the buffers go
   HIPCHK(d, (hipError_t)error.load());
-  HIPCHK(d, sync);
   return RWMI_OK;
 }
 
