@@ -194,7 +194,9 @@ typedef struct rwmi_batch rwmi_batch;
 rwmi_status rwmi_create_domain(const rwmi_domain_desc* desc, rwmi_domain** out);
 
 /* Release every device buffer of the domain (after synchronising its stream).
- * NULL is ignored.  A domain still in a batch is removed from it first. */
+ * NULL is ignored.  A domain still in a batch is removed from it first.  The
+ * process's last domain also gives back the pinned host memory that large
+ * read-outs use (at most 64 MB for all domains), which waits for the device. */
 void rwmi_destroy_domain(rwmi_domain* dom);
 
 /* Add a metaball particle (Eq. 3) with prescribed motion.  The host arrays are

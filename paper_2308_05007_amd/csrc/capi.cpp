@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -205,9 +206,9 @@ void release(rwmi_domain* d, void* p) {
 // Up to 24 MB the copies go straight to the caller, or, to be widened or
 // deinterleaved, up to 8 MB through one host buffer.  Beyond that the caller's
 // pages are mostly new, and one thread writing them reaches 4-9 GB/s, eight
-// threads 60, the link 48 through pinned memory: chunks go through pinned
-// buffers of this call, one per worker, which waits for its chunk in its buffer
-// and lays it out while the others' chunks are on the link.  Workers end with the
+// threads 60, the link 48 through pinned memory: chunks go through a pinned
+// buffer, a part of it per worker, which waits for its chunk there and lays it
+// out while the others' chunks are on the link.  Workers end with the
 // call; without them (or pinned memory) the calling thread does it all.  Below
 // the limits starting them, and the first touch of the pinned pages, cost what
 // they gain (distributions of 48^3, 17 MB: 0.7-2.3 ms with them, 1.0 without;
@@ -253,33 +254,69 @@ constexpr size_t kCopyChunk = 2u << 20;
 constexpr size_t kDirectBytes = 24u << 20;  // bytes to be laid out count three times
 constexpr int kCopyWorkers = 8;
 
-// A host buffer for copies, pinned if it can be.  Another thread's stream
-// capture is not disturbed by the allocation.
-struct CopyBuffer {
-  char* p = nullptr;
-  bool pinned = false;
-  CopyBuffer(size_t bytes, bool pin) {
-    if (pin) {
-      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-      (void)hipThreadExchangeStreamCaptureMode(&mode);
-      pinned = hipHostMalloc((void**)&p, bytes, hipHostMallocDefault) == hipSuccess;
-      if (!pinned) {
-        (void)hipGetLastError();
-        p = nullptr;
-      }
-      (void)hipThreadExchangeStreamCaptureMode(&mode);
+// The pinned buffers of large read-outs.  Freeing pinned memory waits for the
+// whole device (a read-out of 128^3 beside another domain's queued steps took
+// 220 ms, all of that queue, instead of 2-9), so they are kept for the next
+// read-out of any domain and given back when the process's last domain goes.
+// At most kMax: a read-out that finds them all in use gets none and copies
+// through pageable memory.
+class PinnedBuffers {
+ public:
+  static constexpr int kMax = 4;
+  static constexpr size_t kBytes = kCopyChunk * (size_t)kCopyWorkers;
+  char* take() {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (n_free_ > 0) return free_[--n_free_];
+    if (n_ == kMax) return nullptr;
+    void* p = nullptr;
+    const Relaxed mode;
+    if (hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
     }
-    if (!p) p = (char*)std::malloc(bytes);
+    ++n_;
+    return (char*)p;
+  }
+  void give(char* p) {
+    std::lock_guard<std::mutex> lk(mu_);
+    free_[n_free_++] = p;
+  }
+  void domain_created() {
+    std::lock_guard<std::mutex> lk(mu_);
+    ++domains_;
+  }
+  void domain_destroyed() {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (--domains_ > 0) return;
+    const Relaxed mode;
+    while (n_free_ > 0) (void)hipHostFree(free_[--n_free_]);
+    n_ = 0;
+  }
+
+ private:
+  // Another thread's stream capture is not disturbed by these calls.
+  struct Relaxed {
+    hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&m); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&m); }
+  };
+  std::mutex mu_;
+  char* free_[kMax];
+  int n_ = 0, n_free_ = 0;  // allocated; of them, not in use
+  int64_t domains_ = 0;
+};
+PinnedBuffers g_pinned;
+
+// The host buffer of one read-out: one of the pinned ones, or pageable.
+struct CopyBuffer {
+  char* pinned;
+  char* p;
+  CopyBuffer(size_t bytes, bool pin) : pinned(pin ? g_pinned.take() : nullptr) {
+    p = pinned ? pinned : (char*)std::malloc(bytes);
   }
   ~CopyBuffer() {
-    if (!pinned) {
-      std::free(p);
-      return;
-    }
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    (void)hipHostFree(p);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (pinned) g_pinned.give(pinned);
+    else std::free(p);
   }
   CopyBuffer(const CopyBuffer&) = delete;
   CopyBuffer& operator=(const CopyBuffer&) = delete;
@@ -324,8 +361,8 @@ rwmi_status copy_out(rwmi_domain* d, const Piece* pieces, int n) {
   // in each worker.
   HIPCHK(d, hipStreamSynchronize(d->stream));
   const int workers = (int)std::min<size_t>(kCopyWorkers, chunks);
-  CopyBuffer buf(kCopyChunk * (size_t)workers, true);
-  if (!buf.p) return fail(d, RWMI_ENOMEM, "host allocation of %zu bytes failed", kCopyChunk * (size_t)workers);
+  CopyBuffer buf(PinnedBuffers::kBytes, true);
+  if (!buf.p) return fail(d, RWMI_ENOMEM, "host allocation of %zu bytes failed", PinnedBuffers::kBytes);
   std::atomic<size_t> next{0};
   std::atomic<int> error{(int)hipSuccess};
   auto work = [&](int w) {
@@ -898,6 +935,7 @@ rwmi_status rwmi_create_domain(const rwmi_domain_desc* s, rwmi_domain** out) {
     }
     d->own_stream = true;
   }
+  g_pinned.domain_created();
   DomView& v = d->hv;
   std::memset(&v, 0, sizeof v);
   for (int a = 0; a < 3; ++a) {
@@ -991,6 +1029,7 @@ void rwmi_destroy_domain(rwmi_domain* d) {
   for (void* p : d->owned) dev_free(d->al, p);
   if (d->own_stream) (void)hipStreamDestroy(d->stream);
   delete d;
+  g_pinned.domain_destroyed();
 }
 
 rwmi_status rwmi_add_metaball_particle(rwmi_domain* d, const rwmi_metaball_desc* p, int32_t* out_id) {

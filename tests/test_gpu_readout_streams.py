@@ -41,3 +41,45 @@ def test_per_thread_stream(B, monkeypatch):
         b.step(300)  # still in the queue when the read-out is called
         for x, y in zip(read(a), read(b)):
             assert np.array_equal(x, y)
+
+
+def test_readouts_do_not_wait_for_other_domains(B):
+    """A read-out waits for its own domain's stream: another domain's queue
+    (some 300 ms) is still running when a read-out of a few ms returns, the
+    first of the process's as well as later ones."""
+    other = B.build_domain(_cfg((256, 256, 256), 1_000))
+    other.step(4)
+    other.sync()
+    a = B.build_domain(_cfg())
+    a.step(2)
+    for read in (B.Domain.velocity, B.Domain.walkers, B.Domain.distributions):
+        a.sync()
+        other.step(800)
+        read(a)
+        assert not other._torch_stream.query(), "the read-out waited for the whole device"
+        other.sync()
+
+
+def test_concurrent_readouts(B):
+    """More read-outs at a time than there are pinned buffers."""
+    import threading
+    cfg = _cfg()
+    doms = [B.build_domain(cfg) for _ in range(6)]
+    for d in doms:
+        d.step(3)
+    want = doms[0].velocity()
+    got = [None] * len(doms)
+
+    def work(i):
+        for _ in range(3):
+            got[i] = doms[i].velocity()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(doms))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for u, rho in got:
+        assert np.array_equal(u, want[0]) and np.array_equal(rho, want[1])
+    for d in doms:
+        d.close()
