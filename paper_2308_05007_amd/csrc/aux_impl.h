@@ -170,11 +170,13 @@ __global__ void __launch_bounds__(kProfileThreads) k_profile(const DomView* __re
 // 256 on a large one, where a block's other threads wait for the wave that
 // culls the particles (launch_moments).
 //
-// Walkers: their sums are exact, so any order gives the same result: every
-// term is split into three integers (ExactSum), the integers are added, and
-// one rounding at the end makes the double.  Walkers are so read slot by slot,
+// Walkers: every term is rounded to a multiple of 2^-59 and split into three
+// integers (ExactSum); the integers' sums are exact, so any order gives the
+// same result, and are combined into a double at the end.  Walkers are so read slot by slot,
 // coalesced.  In id order (a gather through the id map, 28 scattered bytes a
 // walker) the same sums took 1.19 ms for 1e7 walkers, and the map 0.13 ms.
+// Reference points so far off (2^30.5 lattice units), or not finite, that the
+// squares are beyond those integers get sums in double, walkers in id order.
 constexpr int kRedThreads = 1024;
 constexpr int kRedRows = kRedThreads / 16;
 constexpr int kRedChunk = 4096;       // nodes per block
@@ -183,10 +185,12 @@ constexpr int kWalkMom = 6;           // sum d[3], sum d^2[3]
 constexpr int kWalkWords = 3 * kWalkMom;
 constexpr int kNodeMom = 12;          // rho, rho u[3], (1-eps) u[3], (1-eps), eps us[3], eps
 
-// Sum of doubles below 2^81 in magnitude, exact to 2^-59 per term: x = h 2^30
-// + m 2^-10 + l 2^-59 with each remainder exact (powers of two only), |m| <=
-// 2^39, |l| <= 2^48.  `carry` brings the digits back to those ranges, so that
-// 2^14 terms, or 2^14 carried sums, fit in 64 bits.
+// Sum of doubles below 2^61 in magnitude, exact to 2^-59 per term: x = h 2^30
+// + m 2^-10 + l 2^-59 with each remainder exact (powers of two only), |h| <=
+// 2^31, |m| <= 2^39, |l| <= 2^48.  `carry` brings m and l back to those ranges,
+// so that 2^14 terms, or 2^14 carried sums, fit in 64 bits; the h of 2^31 terms
+// always do.
+constexpr double kExactMax = 0x1p61;
 struct ExactSum {
   long long h = 0, m = 0, l = 0;
   // the nearest integer to t (|t| < 2^51) as the low bits of t + 1.5 2^52
@@ -265,10 +269,12 @@ struct MomRef {
   double x[3];
 };
 
-// part[chunk][3 k + digit]: the chunk's carried sums.
+// part[chunk][3 k + digit]: the chunk's carried sums.  *range is set where a
+// term is beyond ExactSum's range (or is not finite): the sums are then made by
+// k_mom_walkers_by_id instead.
 template <typename R>
 __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __restrict__ views, int dom, MomRef ref,
-                                                             long long* __restrict__ part) {
+                                                             long long* __restrict__ part, double* __restrict__ range) {
   __shared__ long long sh[kRedRows][kWalkWords];
   const DomView& V = views[dom];
   const auto off = gp((const R*)V.woff);
@@ -276,6 +282,7 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __re
   const auto cell = gp((const int32_t*)V.wcell);
   const int64_t nw = V.nw, base = (int64_t)blockIdx.x * kWalkChunk;
   ExactSum sum[kWalkMom];
+  bool beyond = false;
 #pragma unroll 4
   for (int j = 0; j < kWalkChunk / kRedThreads; ++j) {
     const int64_t w = base + (int64_t)j * kRedThreads + threadIdx.x;
@@ -288,10 +295,12 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __re
     for (int a = 0; a < 3; ++a) {
       const int64_t X = (int64_t)c[a] + (int64_t)img[a * nw + w] * (int64_t)V.n[a];
       const double dv = ((double)X - ref.x[a]) + (double)off[a * nw + w];
+      beyond |= !(dv * dv < kExactMax);
       sum[a].add(dv);
       sum[3 + a].add(dv * dv);
     }
   }
+  if (beyond) *range = 1.0;  // by as many threads as find it
   long long acc[kWalkWords];
 #pragma unroll
   for (int k = 0; k < kWalkMom; ++k) {
@@ -315,14 +324,70 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __re
   }
 }
 
+// The same sums added in double, in an order of the walkers' ids that is fixed:
+// for displacements whose squares ExactSum does not hold.  cell, off, img: the
+// walkers in id order (k_read_walkers).  Thread j adds walkers j, j + 256, ...
+// of its block's chunk, the block folds by halves, k_mom_by_id_final adds the
+// chunks in turn.
+constexpr int kIdThreads = 256;
+template <typename R>
+__global__ void __launch_bounds__(kIdThreads) k_mom_walkers_by_id(const DomView* __restrict__ views, int dom,
+                                                                  MomRef ref, const int32_t* __restrict__ cell,
+                                                                  const R* __restrict__ off,
+                                                                  const int32_t* __restrict__ img,
+                                                                  double* __restrict__ part) {
+  __shared__ double sh[kWalkMom][kIdThreads];
+  const DomView& V = views[dom];
+  const int64_t nw = V.nw, base = (int64_t)blockIdx.x * kRedChunk;
+  const int tid = threadIdx.x;
+  double acc[kWalkMom] = {0, 0, 0, 0, 0, 0};
+  for (int j = tid; j < kRedChunk; j += kIdThreads) {
+    const int64_t w = base + j;
+    if (w >= nw) break;
+    const uint32_t lc = (uint32_t)gp(cell)[w];
+    const uint32_t q1 = fdiv(lc, V.dx);
+    const int cz = (int)fdiv(q1, V.dy);
+    const int c[3] = {(int)(lc - q1 * (uint32_t)V.n[0]), (int)q1 - cz * V.n[1], cz};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int64_t X = (int64_t)c[a] + (int64_t)gp(img)[a * nw + w] * (int64_t)V.n[a];
+      const double dv = ((double)X - ref.x[a]) + (double)gp(off)[a * nw + w];
+      acc[a] = acc[a] + dv;
+      acc[3 + a] = acc[3 + a] + dv * dv;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kWalkMom; ++k) sh[k][tid] = acc[k];
+  __syncthreads();
+  for (int h = kIdThreads / 2; h > 0; h >>= 1) {
+    if (tid < h) {
+#pragma unroll
+      for (int k = 0; k < kWalkMom; ++k) sh[k][tid] = sh[k][tid] + sh[k][tid + h];
+    }
+    __syncthreads();
+  }
+  if (tid < kWalkMom) part[(int64_t)blockIdx.x * kWalkMom + tid] = sh[tid][0];
+}
+
+__global__ void __launch_bounds__(64) k_mom_by_id_final(const double* __restrict__ part, int64_t chunks,
+                                                        double* __restrict__ out) {
+  const int tid = threadIdx.x;
+  if (tid >= kWalkMom) return;
+  double s = 0.0;
+  for (int64_t b = 0; b < chunks; ++b) s = s + gp(part)[b * kWalkMom + tid];
+  out[tid] = s;
+}
+
+// *range is cleared for the walkers' kernel, which runs after this one.
 template <typename U, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict__ views, int dom,
-                                                           double* __restrict__ part) {
+                                                       double* __restrict__ part, double* __restrict__ range) {
   __shared__ double sh[THREADS / 16][kNodeMom];
   using C = typename Store<sizeof(U) == 8 ? P64 : P32>::C;
   __shared__ BlockParticles<C> sp;
   const DomView& V = views[dom];
   const uint32_t N = (uint32_t)V.N;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *range = 0.0;
   const uint32_t base = blockIdx.x * (uint32_t)kRedChunk;
   const uint32_t last = base + kRedChunk - 1 < N ? base + kRedChunk - 1 : N - 1;
   const uint64_t done = V.tstep[0];  // steps completed
@@ -389,7 +454,8 @@ __global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict
     part[(int64_t)blockIdx.x * kNodeMom + (threadIdx.x >> 4)] = s;
 }
 
-// out: [0..5] walker sums, [6..17] node sums, [18..25] counters, [26] step.
+// out: [0..5] walker sums, [6..17] node sums, [18..25] counters, [26] step, and
+// kMomRange, which the other kernels write.
 // One block; one thread adding the chunks in turn took 1.2 ms for the 4096
 // chunks of a 256^3 lattice.
 __global__ void __launch_bounds__(kRedThreads) k_mom_final(const DomView* __restrict__ views, int dom,
@@ -406,6 +472,18 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_final(const DomView* __rest
   for (int64_t b = tid; b < nbw; b += kRedThreads)
 #pragma unroll
     for (int k = 0; k < kWalkWords; ++k) aw[k] += gp(pw)[b * kWalkWords + k];
+  // up to 2^7 chunks a thread, 2^10 threads: carried in between
+#pragma unroll
+  for (int k = 0; k < kWalkMom; ++k) {
+    ExactSum e;
+    e.h = aw[3 * k];
+    e.m = aw[3 * k + 1];
+    e.l = aw[3 * k + 2];
+    e.carry();
+    aw[3 * k] = e.h;
+    aw[3 * k + 1] = e.m;
+    aw[3 * k + 2] = e.l;
+  }
   double an[kNodeMom];
 #pragma unroll
   for (int k = 0; k < kNodeMom; ++k) an[k] = 0.0;

@@ -1516,6 +1516,21 @@ rwmi_status rwmi_read_profile(rwmi_domain* d, int32_t axis, uint64_t* counts) {
   return RWMI_OK;
 }
 
+// The moments from launch_moments' partials pw and output outd, which are
+// copied to h.
+static rwmi_status finish_moments(rwmi_domain* d, double* pw, double* outd, rwmi_moments* out) {
+  double h[32];
+  HIPCHK(d, hipMemcpyAsync(h, outd, sizeof h, hipMemcpyDeviceToHost, d->stream));
+  HIPCHK(d, hipStreamSynchronize(d->stream));
+  if (d->hv.nw > 0 && h[rwmi::kMomRange] != 0.0) {
+    HIPCHK(d, rwmi::launch_walker_sums_by_id(d->prec, d->dv, 0, d->hv.nw, d->sort, d->ref, pw, outd, d->stream));
+    HIPCHK(d, hipMemcpyAsync(h, outd, 48, hipMemcpyDeviceToHost, d->stream));
+    HIPCHK(d, hipStreamSynchronize(d->stream));
+  }
+  fill_moments(d, h, out);
+  return RWMI_OK;
+}
+
 rwmi_status rwmi_read_moments(rwmi_domain* d, rwmi_moments* out) {
   if (!d || !out) return fail(d, RWMI_EINVAL, "null argument");
   HIPCHK(d, hipSetDevice(d->device));
@@ -1533,11 +1548,7 @@ rwmi_status rwmi_read_moments(rwmi_domain* d, rwmi_moments* out) {
   if (!d->mom_out && (st = alloc_into(d, d->mom_out, 8 * 32)) != RWMI_OK) return st;
   HIPCHK(d, rwmi::launch_moments(d->prec, d->dv, 0, N, nw, d->ref, d->mom_part, d->mom_part + words, d->mom_out,
                                  d->stream));
-  double h[32];
-  const Piece p = {Piece::kBytes, h, d->mom_out, (int64_t)sizeof h};
-  if ((st = copy_out(d, &p, 1)) != RWMI_OK) return st;
-  fill_moments(d, h, out);
-  return RWMI_OK;
+  return finish_moments(d, d->mom_part, d->mom_out, out);
 }
 
 // Same kernels as rwmi_read_moments, with every buffer they need (output
@@ -1565,11 +1576,7 @@ rwmi_status rwmi_read_moments_noalloc(rwmi_domain* d, rwmi_moments* out) {
   double* pw = sc + 40;
   double* pn = pw + rwmi::moment_walker_words(nw);
   HIPCHK(d, rwmi::launch_moments(d->prec, d->dv, 0, N, nw, d->ref, pw, pn, outd, d->stream));
-  double h[32];
-  HIPCHK(d, hipMemcpyAsync(h, outd, sizeof h, hipMemcpyDeviceToHost, d->stream));
-  HIPCHK(d, hipStreamSynchronize(d->stream));
-  fill_moments(d, h, out);
-  return RWMI_OK;
+  return finish_moments(d, pw, outd, out);
 }
 
 rwmi_status rwmi_debug_set(rwmi_domain* d, int32_t key, int64_t value) {

@@ -7,8 +7,7 @@
 #include "launch.h"
 #include "step_impl.h"
 
-// Moment partials, staging output and reference point of the allocation-free
-// moment read-out.  In host code this name is only a stand-in for the symbol:
+// Moment partials and staging output of the allocation-free moment read-out.  In host code this name is only a stand-in for the symbol:
 // kernels get the address noalloc_scratch looked up on their device.
 static __device__ __align__(256) double scratch[rwmi::kNoAllocDoubles];
 
@@ -151,9 +150,9 @@ hipError_t launch_profile(const DomView* v, int dom, int axis, int n_layers, int
 constexpr int64_t kMomWideChunks = 1024;
 
 template <typename U>
-static void mom_nodes(bool wide, unsigned nbn, const DomView* v, int dom, double* pn, hipStream_t s) {
-  if (wide) k_mom_nodes<U, 1024><<<nbn, 1024, 0, s>>>(v, dom, pn);
-  else k_mom_nodes<U, 256><<<nbn, 256, 0, s>>>(v, dom, pn);
+static void mom_nodes(bool wide, unsigned nbn, const DomView* v, int dom, double* pn, double* range, hipStream_t s) {
+  if (wide) k_mom_nodes<U, 1024><<<nbn, 1024, 0, s>>>(v, dom, pn, range);
+  else k_mom_nodes<U, 256><<<nbn, 256, 0, s>>>(v, dom, pn, range);
 }
 
 hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double ref[3], double* pw,
@@ -162,14 +161,29 @@ hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_
   const int64_t nbn = (N + kRedChunk - 1) / kRedChunk;
   const MomRef r{{ref[0], ref[1], ref[2]}};
   long long* iw = (long long*)pw;
-  if (nbw > 0) {
-    if (prec == P64) k_mom_walkers<double><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, r, iw);
-    else k_mom_walkers<float><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, r, iw);
-  }
+  double* range = out + kMomRange;
   const bool wide = nbn < kMomWideChunks;
-  if (prec == P64) mom_nodes<double>(wide, (unsigned)nbn, v, dom, pn, s);
-  else mom_nodes<float>(wide, (unsigned)nbn, v, dom, pn, s);
+  if (prec == P64) mom_nodes<double>(wide, (unsigned)nbn, v, dom, pn, range, s);
+  else mom_nodes<float>(wide, (unsigned)nbn, v, dom, pn, range, s);
+  if (nbw > 0) {
+    if (prec == P64) k_mom_walkers<double><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, r, iw, range);
+    else k_mom_walkers<float><<<(unsigned)nbw, kRedThreads, 0, s>>>(v, dom, r, iw, range);
+  }
   k_mom_final<<<1, kRedThreads, 0, s>>>(v, dom, iw, nbw, pn, nbn, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_walker_sums_by_id(int prec, const DomView* v, int dom, int64_t nw, const SortScratch& sc,
+                                    const double ref[3], double* pw, double* out, hipStream_t s) {
+  const hipError_t e = launch_read_walkers(prec, v, dom, nw, sc, s);
+  if (e != hipSuccess) return e;
+  const int64_t chunks = (nw + kRedChunk - 1) / kRedChunk;
+  const MomRef r{{ref[0], ref[1], ref[2]}};
+  const unsigned g = (unsigned)chunks;
+  if (prec == P64)
+    k_mom_walkers_by_id<double><<<g, kIdThreads, 0, s>>>(v, dom, r, sc.cell, (const double*)sc.off, sc.img, pw);
+  else k_mom_walkers_by_id<float><<<g, kIdThreads, 0, s>>>(v, dom, r, sc.cell, (const float*)sc.off, sc.img, pw);
+  k_mom_by_id_final<<<1, 64, 0, s>>>(pw, chunks, out);
   return hipGetLastError();
 }
 

@@ -47,7 +47,9 @@ hipError_t launch_occupancy(const DomView* v, int dom, uint32_t* occ, int64_t N,
 hipError_t launch_profile(const DomView* v, int dom, int axis, int n_layers, int64_t nw, uint32_t* counts,
                           hipStream_t s);
 // partial buffers: walkers moment_walker_words(nw) (18 per 16384), nodes
-// ceil(N/4096)*12 words of 8 bytes; ref: the walkers' reference point (host)
+// ceil(N/4096)*12 words of 8 bytes; ref: the walkers' reference point (host).
+// out[kMomRange] nonzero: the walkers' sums need launch_walker_sums_by_id
+constexpr int kMomRange = 27;
 int64_t moment_walker_blocks(int64_t nw);
 int64_t moment_walker_words(int64_t nw);
 hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double ref[3],
@@ -86,6 +88,10 @@ hipError_t launch_sort(int prec, const DomView* views, int dom, int64_t nw, cons
 // slots' ids are corrupt.
 hipError_t launch_read_walkers(int prec, const DomView* views, int dom, int64_t nw, const SortScratch& sc,
                                hipStream_t s);
+// The walkers' six moment sums in double, walkers in id order (which it leaves
+// in sc): out[0..5].  pw: 6 doubles per 4096 walkers.
+hipError_t launch_walker_sums_by_id(int prec, const DomView* v, int dom, int64_t nw, const SortScratch& sc,
+                                    const double ref[3], double* pw, double* out, hipStream_t s);
 // Slot i holds walker i (after seeding).
 hipError_t launch_ids_identity(const DomView* views, int dom, int64_t nw, hipStream_t s);
 hipError_t launch_normals(uint64_t seed, uint32_t t, uint32_t purpose, int64_t n, double* z, hipStream_t s);
