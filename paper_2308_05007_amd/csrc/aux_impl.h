@@ -170,13 +170,15 @@ __global__ void __launch_bounds__(kProfileThreads) k_profile(const DomView* __re
 // 256 on a large one, where a block's other threads wait for the wave that
 // culls the particles (launch_moments).
 //
-// Walkers: every term is rounded to a multiple of 2^-59 and split into three
+// Walkers: every term is rounded to a multiple of 2^-76 and split into three
 // integers (ExactSum); the integers' sums are exact, so any order gives the
 // same result, and are combined into a double at the end.  Walkers are so read slot by slot,
 // coalesced.  In id order (a gather through the id map, 28 scattered bytes a
 // walker) the same sums took 1.19 ms for 1e7 walkers, and the map 0.13 ms.
-// Reference points so far off (2^30.5 lattice units), or not finite, that the
-// squares are beyond those integers get sums in double, walkers in id order.
+// Displacements whose squares those integers do not hold (2^25.5 lattice units,
+// or a reference point that is not finite) or hold in too few bits (2^-11) get
+// sums in double, walkers in id order: a read-out with 1e7 walkers then takes
+// 1.60 ms instead of 0.26 (in double for all walkers it took 2.83).
 constexpr int kRedThreads = 1024;
 constexpr int kRedRows = kRedThreads / 16;
 constexpr int kRedChunk = 4096;       // nodes per block
@@ -185,12 +187,17 @@ constexpr int kWalkMom = 6;           // sum d[3], sum d^2[3]
 constexpr int kWalkWords = 3 * kWalkMom;
 constexpr int kNodeMom = 12;          // rho, rho u[3], (1-eps) u[3], (1-eps), eps us[3], eps
 
-// Sum of doubles below 2^61 in magnitude, exact to 2^-59 per term: x = h 2^30
-// + m 2^-10 + l 2^-59 with each remainder exact (powers of two only), |h| <=
-// 2^31, |m| <= 2^39, |l| <= 2^48.  `carry` brings m and l back to those ranges,
-// so that 2^14 terms, or 2^14 carried sums, fit in 64 bits; the h of 2^31 terms
-// always do.
-constexpr double kExactMax = 0x1p61;
+// Sum of doubles below 2^51 in magnitude, exact to 2^-76 per term: x = h 2^20
+// + m 2^-28 + l 2^-76 with each remainder exact (powers of two only), |h| <=
+// 2^31, |m|, |l| <= 2^47.  `carry` brings m and l back to those ranges, so that
+// 2^15 terms, or 2^15 carried sums, fit in 64 bits; the h of 2^31 terms always
+// do.  A square of 2^-22 or more (a displacement of 5e-4) keeps all its bits,
+// so a sum of squares of at least kExactMin per walker is held to half of
+// its last place, and the sum of the displacements far better.  (With the last
+// digit at 2^-59, 1000 squares of displacements of 1e-6 were off by 1e-8 of
+// their sum.  A fourth digit instead of sums in double for such displacements:
+// 101 us for 1e7 walkers, with three 85.)
+constexpr double kExactMax = 0x1p51;
 struct ExactSum {
   long long h = 0, m = 0, l = 0;
   // the nearest integer to t (|t| < 2^51) as the low bits of t + 1.5 2^52
@@ -201,26 +208,26 @@ struct ExactSum {
     return __double_as_longlong(s) - __double_as_longlong(magic);
   }
   __device__ __forceinline__ void add(double x) {
-    double t = x * 0x1p-30;
+    double t = x * 0x1p-20;
     h += digit(t);
-    x = x - t * 0x1p30;
-    t = x * 0x1p10;
+    x = x - t * 0x1p20;
+    t = x * 0x1p28;
     m += digit(t);
-    x = x - t * 0x1p-10;
-    t = x * 0x1p59;
+    x = x - t * 0x1p-28;
+    t = x * 0x1p76;
     l += digit(t);
   }
   __device__ __forceinline__ void carry() {
-    const long long c = (l + (1ll << 48)) >> 49;
-    l -= c << 49;
+    const long long c = (l + (1ll << 47)) >> 48;
+    l -= c << 48;
     m += c;
-    const long long d = (m + (1ll << 39)) >> 40;
-    m -= d << 40;
+    const long long d = (m + (1ll << 47)) >> 48;
+    m -= d << 48;
     h += d;
   }
   __device__ __forceinline__ double value() {
     carry();
-    return (double)h * 0x1p30 + ((double)m * 0x1p-10 + (double)l * 0x1p-59);
+    return (double)h * 0x1p20 + ((double)m * 0x1p-28 + (double)l * 0x1p-76);
   }
 };
 
@@ -269,9 +276,9 @@ struct MomRef {
   double x[3];
 };
 
-// part[chunk][3 k + digit]: the chunk's carried sums.  *range is set where a
-// term is beyond ExactSum's range (or is not finite): the sums are then made by
-// k_mom_walkers_by_id instead.
+// part[chunk][3 k + digit]: the chunk's carried sums.  range[0] is set where a
+// term is beyond ExactSum's range (or is not finite), range[1] where a square is
+// below its last digit and not zero.
 template <typename R>
 __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __restrict__ views, int dom, MomRef ref,
                                                              long long* __restrict__ part, double* __restrict__ range) {
@@ -282,7 +289,7 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __re
   const auto cell = gp((const int32_t*)V.wcell);
   const int64_t nw = V.nw, base = (int64_t)blockIdx.x * kWalkChunk;
   ExactSum sum[kWalkMom];
-  bool beyond = false;
+  bool beyond = false, below = false;
 #pragma unroll 4
   for (int j = 0; j < kWalkChunk / kRedThreads; ++j) {
     const int64_t w = base + (int64_t)j * kRedThreads + threadIdx.x;
@@ -296,11 +303,13 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __re
       const int64_t X = (int64_t)c[a] + (int64_t)img[a * nw + w] * (int64_t)V.n[a];
       const double dv = ((double)X - ref.x[a]) + (double)off[a * nw + w];
       beyond |= !(dv * dv < kExactMax);
+      below |= dv != 0.0 && dv * dv < 0x1p-76;
       sum[a].add(dv);
       sum[3 + a].add(dv * dv);
     }
   }
-  if (beyond) *range = 1.0;  // by as many threads as find it
+  if (beyond) range[0] = 1.0;  // by as many threads as find it
+  if (below) range[1] = 1.0;
   long long acc[kWalkWords];
 #pragma unroll
   for (int k = 0; k < kWalkMom; ++k) {
@@ -325,7 +334,7 @@ __global__ void __launch_bounds__(kRedThreads) k_mom_walkers(const DomView* __re
 }
 
 // The same sums added in double, in an order of the walkers' ids that is fixed:
-// for displacements whose squares ExactSum does not hold.  cell, off, img: the
+// for displacements whose squares ExactSum does not hold, or holds badly.  cell, off, img: the
 // walkers in id order (k_read_walkers).  Thread j adds walkers j, j + 256, ...
 // of its block's chunk, the block folds by halves, k_mom_by_id_final adds the
 // chunks in turn.
@@ -378,7 +387,7 @@ __global__ void __launch_bounds__(64) k_mom_by_id_final(const double* __restrict
   out[tid] = s;
 }
 
-// *range is cleared for the walkers' kernel, which runs after this one.
+// range[0..1] is cleared for the walkers' kernel, which runs after this one.
 template <typename U, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict__ views, int dom,
                                                        double* __restrict__ part, double* __restrict__ range) {
@@ -387,7 +396,7 @@ __global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict
   __shared__ BlockParticles<C> sp;
   const DomView& V = views[dom];
   const uint32_t N = (uint32_t)V.N;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *range = 0.0;
+  if (blockIdx.x == 0 && threadIdx.x < 2) range[threadIdx.x] = 0.0;
   const uint32_t base = blockIdx.x * (uint32_t)kRedChunk;
   const uint32_t last = base + kRedChunk - 1 < N ? base + kRedChunk - 1 : N - 1;
   const uint64_t done = V.tstep[0];  // steps completed
@@ -455,7 +464,7 @@ __global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict
 }
 
 // out: [0..5] walker sums, [6..17] node sums, [18..25] counters, [26] step, and
-// kMomRange, which the other kernels write.
+// range (kMomRange), which the other kernels write.
 // One block; one thread adding the chunks in turn took 1.2 ms for the 4096
 // chunks of a 256^3 lattice.
 __global__ void __launch_bounds__(kRedThreads) k_mom_final(const DomView* __restrict__ views, int dom,

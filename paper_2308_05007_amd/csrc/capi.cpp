@@ -1522,7 +1522,10 @@ static rwmi_status finish_moments(rwmi_domain* d, double* pw, double* outd, rwmi
   double h[32];
   HIPCHK(d, hipMemcpyAsync(h, outd, sizeof h, hipMemcpyDeviceToHost, d->stream));
   HIPCHK(d, hipStreamSynchronize(d->stream));
-  if (d->hv.nw > 0 && h[rwmi::kMomRange] != 0.0) {
+  bool by_id = h[rwmi::kMomRange] != 0.0;
+  for (int a = 0; a < 3; ++a)
+    by_id |= h[3 + a] > 0.0 ? h[3 + a] < rwmi::kExactMin * (double)d->hv.nw : h[rwmi::kMomRange + 1] != 0.0;
+  if (d->hv.nw > 0 && by_id) {
     HIPCHK(d, rwmi::launch_walker_sums_by_id(d->prec, d->dv, 0, d->hv.nw, d->sort, d->ref, pw, outd, d->stream));
     HIPCHK(d, hipMemcpyAsync(h, outd, 48, hipMemcpyDeviceToHost, d->stream));
     HIPCHK(d, hipStreamSynchronize(d->stream));

@@ -48,8 +48,11 @@ hipError_t launch_profile(const DomView* v, int dom, int axis, int n_layers, int
                           hipStream_t s);
 // partial buffers: walkers moment_walker_words(nw) (18 per 16384), nodes
 // ceil(N/4096)*12 words of 8 bytes; ref: the walkers' reference point (host).
-// out[kMomRange] nonzero: the walkers' sums need launch_walker_sums_by_id
+// out[kMomRange] nonzero: the walkers' sums need launch_walker_sums_by_id;
+// so does a sum of squares below kExactMin per walker that is not zero, or is
+// and out[kMomRange + 1] nonzero (squares that were rounded to zero)
 constexpr int kMomRange = 27;
+constexpr double kExactMin = 0x1p-22;
 int64_t moment_walker_blocks(int64_t nw);
 int64_t moment_walker_words(int64_t nw);
 hipError_t launch_moments(int prec, const DomView* v, int dom, int64_t N, int64_t nw, const double ref[3],

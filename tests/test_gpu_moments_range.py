@@ -48,3 +48,35 @@ def test_far_references(B, nw, ref, precision):
                 assert abs(got - math.fsum(t)) <= _chain(nw) * np.abs(t).sum() + np.spacing(abs(got)), (got, t[:4])
             else:
                 assert np.array_equal(got, t.sum(), equal_nan=True), (got, t[:4])
+
+
+# From 2^-11 on every term's 53 bits are held, what remains are the roundings of
+# the last combination; below, the sums are in double.
+@pytest.mark.parametrize("nw", (1, 1000, 100_003))
+@pytest.mark.parametrize("scale", (1e-1, 5e-3, 5e-4, 1e-5, 1e-6, 1e-12, 1e-25))
+def test_small_displacements(B, nw, scale):
+    n, ref = (18, 15, 21), (0.0, 0.0, 0.0)
+    xyz = scale * (0.5 + np.random.default_rng(nw).uniform(size=(nw, 3)))
+    dom = W._domain(n, ("periodic",) * 3, 0.8, (0, 0, 0), 0.0, seed=1)
+    g = B.build_domain(dict(domain=dom, walkers=dict(kind="explicit", n=nw, xyz=xyz, ref=ref)))
+    dv = _displacements(g, n, ref)
+    assert np.array_equal(dv, xyz.T)
+    for m in (g.moments(), g.moments(noalloc=True)):
+        for a in range(3):
+            for got, terms in ((m["sum"][a], dv[a]), (m["sumsq"][a], dv[a] * dv[a])):
+                want = math.fsum(terms)
+                tol = 4 * np.spacing(want) if scale >= 5e-3 else (_chain(nw) * want + np.spacing(want))
+                assert abs(got - want) <= tol, (a, got, want)
+
+
+def test_walkers_on_the_reference(B):
+    """All of them, or on two axes, or all but one: sums of zeros are zero."""
+    n, nw, ref = (18, 15, 21), 5000, (8.5, 7.25, 3.0)
+    dom = W._domain(n, ("periodic",) * 3, 0.8, (0, 0, 0), 0.0, seed=1)
+    xyz = np.tile(np.array(ref), (nw, 1))
+    for step in (0.0, 0.25, 1e-9):
+        xyz[nw // 2, 0] = ref[0] + step
+        g = B.build_domain(dict(domain=dom, walkers=dict(kind="explicit", n=nw, xyz=xyz, ref=ref)))
+        dx = xyz[nw // 2, 0] - ref[0]
+        for m in (g.moments(), g.moments(noalloc=True)):
+            assert np.array_equal(m["sum"], [dx, 0.0, 0.0]) and np.array_equal(m["sumsq"], [dx * dx, 0.0, 0.0])
