@@ -93,8 +93,12 @@ inline PairArgs pair_shape(int nx, int ny, int nz) {
   a.ntx = (nx + a.tx - 1) / a.tx;
   a.nty = (ny + a.ty - 1) / a.ty;
   a.cost = -1;
+  const int64_t tiles = (int64_t)a.ntx * a.nty;
   for (int c = 1; c <= (nz + 3) / 4; ++c) {
-    const int64_t rounds = ((int64_t)a.ntx * a.nty * c + 255) / 256;
+    // no larger c can do better once tiles c / 256 rounds of nz / c + 2 planes
+    // are as many (a column of 5e7 planes: 260 steps of the search, not 1e7)
+    if (a.cost >= 0 && tiles * (nz + 2ll * c) >= 256 * a.cost) break;
+    const int64_t rounds = (tiles * c + 255) / 256;
     const int64_t cost = rounds * ((nz + c - 1) / c + 2);
     if (a.cost < 0 || cost < a.cost) {
       a.cost = cost;
