@@ -18,6 +18,7 @@
 #include "dem_impl.h"
 #include "dev_common.h"
 #include "launch.h"
+#include "pair_plan.h"
 
 namespace rwmi {
 // the bandwidth probe (probe.hip)
@@ -119,6 +120,9 @@ struct rwmi_domain {
   size_t mom_part_n = 0;
   double* mom_out = nullptr;
   rwmi_batch* batch = nullptr;
+  // fluid steps in pairs (pair_steps)
+  bool pair_known = false, pairs = false;
+  rwmi::PairArgs pair_args{};
   // two-way coupled particles
   bool dem = false;
   rwmi::DemArgs dem_host{};
@@ -595,20 +599,29 @@ int launch_flags(const rwmi_domain* d) {
 }
 
 // Fluid steps in pairs (pair_impl.h)?  The byte offsets of the lattice and the
-// velocities have to fit 32 bits, and the pass has to be the faster one: a
-// block plane takes some 5.3 us where rows begin at 64-byte sectors and 6.5
-// where they do not, a single step 30.6 ps per node.  us per fluid step, single
-// and paired: 256^3 512, 332; 250^3 484, 404; 224^3 348, 271; 192^3 219, 163;
-// 176^3 170, 143; 1000x120x120 445, 330; and refused 219x187x241 305, 318;
-// 171x193x165 171, 185 (with 20 particles).  Walkers run 45 us per 1e7 slower
-// apart from the fluid, which two walkers per node make as much as a pair gains.
-bool pair_steps(const rwmi_domain* d, rwmi::PairArgs& a) {
+// velocities have to fit 32 bits, and the pass has to be the faster one.
+// Decided at the first step (what it depends on is fixed by then).
+bool pair_steps(rwmi_domain* d, rwmi::PairArgs& a) {
   const DomView& v = d->hv;
-  if (v.inplace || v.ibb || d->dem || d->prec != RWMI_FP32 || v.bc[0] || v.bc[1] || v.bc[2]) return false;
-  if (rwmi::f_elems(v.N) > (1ull << 30) || v.nw > 2 * v.N) return false;
-  a = rwmi::pair_shape(v.n[0], v.n[1], v.n[2]);
-  const double plane_us = v.n[0] % 16 == 0 ? 5.3 : 6.5;
-  return 0.5 * plane_us * (double)a.cost < 0.92 * 30.6e-6 * (double)v.N;
+  if (!d->pair_known) {
+    d->pair_known = true;
+    d->pairs = false;
+    if (v.inplace || v.ibb || d->dem || d->prec != RWMI_FP32 || v.bc[0] || v.bc[1] || v.bc[2]) return false;
+    if (rwmi::f_elems(v.N) > (1ull << 30)) return false;
+    std::vector<rwmi::PairParticle> parts;
+    for (const HostParticle& q : d->parts) {
+      double K = 0.0, bmax2 = 0.0;
+      for (size_t i = 0; i < q.k.size(); ++i) {
+        K += q.k[i];
+        bmax2 = std::max(bmax2, q.b[3 * i] * q.b[3 * i] + q.b[3 * i + 1] * q.b[3 * i + 1] + q.b[3 * i + 2] * q.b[3 * i + 2]);
+      }
+      parts.push_back({{q.c0[0], q.c0[1], q.c0[2]}, std::sqrt(bmax2) + std::sqrt(K) + 1.25, (int)q.k.size()});
+    }
+    d->pair_args = rwmi::pair_shape(v.n[0], v.n[1], v.n[2]);
+    d->pairs = rwmi::pairs_gain(d->pair_args, v.n, v.nw, parts);
+  }
+  a = d->pair_args;
+  return d->pairs;
 }
 
 rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturing) {

@@ -18,8 +18,10 @@
 // plane.  One block of 11 waves fills a CU (100 KB LDS, 146 VGPRs), so the
 // blocks per pass are chosen to fill whole rounds of the chip (pair_shape).
 //
-// Measured, us per fluid step, single and paired: 256^3 508 -> 294, 224^3 348 ->
-// 271, 192^3 219 -> 163.  A pass moves 1.19 times its own bytes (the rims)
+// Measured, us per fluid step without particles, single and paired: 256^3 509 ->
+// 295, 224^3 346 -> 242, 192^3 220 -> 136; with particles a block waits at each
+// plane for the wave that evaluates their control points, where the single
+// step's other waves go on (pairs_gain).  A pass moves 1.19 times its own bytes (the rims)
 // at 5.2 TB/s; tiles 32 x 16 352, 32 x 8 423, 64 x 12 342 at 256^3, and with 4,
 // 8 runs of planes (2, 4 rounds of blocks) instead of 2 the step with particles
 // and walkers 489, 504 instead of 464.
