@@ -288,8 +288,12 @@ rwmi_status rwmi_seed_walkers(rwmi_domain* dom, const rwmi_seed_desc* s, uint64_
  * (w, t, purpose, 0) with purpose 0 Brownian, 1 refill direction, 2 refill
  * radius.  n steps are n + 1 launches of one fused kernel on the domain
  * stream (launch j: fluid and prologue of step t0 + j, walkers of step
- * t0 + j - 1).  Device-side anomalies are counted (see rwmi_moments), never
- * returned. */
+ * t0 + j - 1).  On large periodic FP32 domains (two lattices, prescribed
+ * particles) where it is faster, the fluid updates of a call are taken two at
+ * a time, each two in one launch of their own after launch j, j even, and
+ * launches j and j + 1 carry what is left; the values are the same bit for
+ * bit (rwmi_query_paired).  Device-side anomalies are counted (see
+ * rwmi_moments), never returned. */
 rwmi_status rwmi_step(rwmi_domain* dom, uint32_t n_steps);
 
 /* Compute and copy the FP64 moments (synchronises). */
@@ -298,7 +302,7 @@ rwmi_status rwmi_read_moments(rwmi_domain* dom, rwmi_moments* out);
 /* For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same moments,
  * bit for bit, from the same kernels, with no allocation of any kind.  The
- * reduction's partials, staging output and reference point live in one
+ * reduction's partials and staging output live in one
  * file-scope device array of the library, 1 MiB per GPU (131072 doubles),
  * which each GPU the library runs on holds until the process ends.  Limit:
  * 64 + 6 ceil(n_walkers / 4096) + 12 ceil(n_nodes / 4096) <= 131072 (the
@@ -337,6 +341,10 @@ rwmi_status rwmi_read_distributions(rwmi_domain* dom, double* f);
 /* Sizes for the read buffers and the number of steps enqueued so far. */
 rwmi_status rwmi_query_sizes(const rwmi_domain* dom, uint64_t* n_nodes, uint64_t* n_walkers, uint64_t* step);
 
+/* How many of the fluid updates enqueued so far were taken two at a time
+ * (rwmi_step): an even number, 0 where the domain is never stepped so. */
+rwmi_status rwmi_query_paired(const rwmi_domain* dom, uint64_t* updates);
+
 /* Device bytes a domain with these parameters holds (for admission by HBM
  * footprint).  Does not touch the device. */
 uint64_t rwmi_footprint_bytes(const rwmi_domain_desc* desc, uint32_t n_particles, uint32_t n_ctrl_total,
@@ -353,7 +361,11 @@ uint64_t rwmi_footprint_bytes(const rwmi_domain_desc* desc, uint32_t n_particles
  *   RWMI_KEY_STEP_FLAGS      launch options of the step kernel: bit 0 deals each of
  *                            the 8 XCDs a contiguous run of fluid blocks with its
  *                            share of walker blocks interleaved (default on), bit 1
- *                            writes f* and u with non-temporal stores
+ *                            writes f* and u with non-temporal stores.  This and
+ *                            RWMI_KEY_BLOCK do not apply to launches of two fluid
+ *                            updates (rwmi_step), which have a shape of their own,
+ *                            deal each XCD a contiguous run and store f* and u
+ *                            non-temporally; a lattice streamed in place has none
  *   RWMI_KEY_SORT_EVERY      regroup the walkers by coarse block (4^3 nodes) every this
  *                            many steps for memory locality (default 128, 0 = never)
  *   RWMI_KEY_STREAMING       1: two lattices (pull from one, write the other); 2: one
@@ -361,7 +373,8 @@ uint64_t rwmi_footprint_bytes(const rwmi_domain_desc* desc, uint32_t n_particles
  *                            distributions take at most 384 MB, else two lattices.
  *                            Only before the first step (ESTATE after); resets f to f^eq
  * Results never depend on the block size, flags or sort interval: walker ids
- * travel with the walkers and every read-out is by id. */
+ * travel with the walkers, read-outs of walkers are in id order, and their
+ * moment sums do not depend on the order. */
 enum {
   RWMI_KEY_MAX_BISECT = 1,
   RWMI_KEY_USE_GRAPH = 2,
@@ -378,10 +391,12 @@ rwmi_status rwmi_debug_set(rwmi_domain* dom, int32_t key, int64_t value);
  * (synchronises, then clears the record): *ms total milliseconds between the
  * events bracketing each timed window of consecutive step launches (windows
  * close before a walker regrouping and at the end of a launch group, so they
- * hold step launches only), *launches the launches timed, and how many of
- * them carried a fluid update (*fluid_steps) and a walker step
- * (*walker_steps); a group of n steps is n + 1 launches, the first without
- * walkers, the last with walkers only. */
+ * hold step launches only), *launches the launches timed, and how many fluid
+ * updates (*fluid_steps) and walker steps (*walker_steps) they carried.  A
+ * group of n steps is n + 1 launches with at most one of each, the first
+ * without walkers, the last with walkers only; where fluid updates are taken
+ * two at a time (rwmi_step) each two are a launch more, which carries no
+ * walkers, and launches that so carry nothing are left out. */
 rwmi_status rwmi_read_kernel_times(rwmi_domain* dom, double* ms, uint64_t* launches, uint64_t* fluid_steps,
                                    uint64_t* walker_steps);
 

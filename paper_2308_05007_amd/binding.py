@@ -110,6 +110,7 @@ SIGNATURES = {
     "rwmi_query_sizes": (C.c_int, [C.c_void_p, C.POINTER(C.c_uint64), C.POINTER(C.c_uint64), C.POINTER(C.c_uint64)]),
     "rwmi_footprint_bytes": (C.c_uint64, [C.POINTER(DomainDesc), C.c_uint32, C.c_uint32, C.c_uint64]),
     "rwmi_debug_set": (C.c_int, [C.c_void_p, C.c_int32, C.c_int64]),
+    "rwmi_query_paired": (C.c_int, [C.c_void_p, C.POINTER(C.c_uint64)]),
     "rwmi_read_kernel_times": (C.c_int, [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_uint64),
                                          C.POINTER(C.c_uint64), C.POINTER(C.c_uint64)]),
     "rwmi_read_coupling_times": (C.c_int, [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_uint64),
@@ -385,6 +386,12 @@ class Domain:
         self._ck(self.L.rwmi_query_sizes(self.h, C.byref(a), C.byref(b), C.byref(c)))
         return int(a.value), int(b.value), int(c.value)
 
+    def paired(self):
+        """Fluid updates so far that were taken two per pass over the lattice."""
+        c = C.c_uint64()
+        self._ck(self.L.rwmi_query_paired(self.h, C.byref(c)))
+        return int(c.value)
+
     def moments(self, noalloc=False):
         """FP64 moments; noalloc=True reads them through the allocation-free
         entry point (same kernels, scratch in the library's device array)."""
@@ -432,8 +439,8 @@ class Domain:
         return f.reshape(19, *self.n[::-1])
 
     def kernel_times(self):
-        """(total ms, launches, of which with a fluid update, of which with a
-        walker step) of the step launches timed since the last call."""
+        """(total ms, launches, fluid updates and walker steps they carried) of
+        the step launches timed since the last call."""
         ms, n, nf, nw = C.c_double(), C.c_uint64(), C.c_uint64(), C.c_uint64()
         self._ck(self.L.rwmi_read_kernel_times(self.h, C.byref(ms), C.byref(n), C.byref(nf), C.byref(nw)))
         return ms.value, int(n.value), int(nf.value), int(nw.value)

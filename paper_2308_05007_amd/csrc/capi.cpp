@@ -123,6 +123,9 @@ struct rwmi_domain {
   // fluid steps in pairs (pair_steps)
   bool pair_known = false, pairs = false;
   rwmi::PairArgs pair_args{};
+  uint64_t paired = 0;        // fluid updates so taken
+  uint32_t group_paired = 0;  // of the group enqueued last
+  uint32_t graph_paired = 0;  // of a replay of gexec
   // two-way coupled particles
   bool dem = false;
   rwmi::DemArgs dem_host{};
@@ -625,6 +628,7 @@ bool pair_steps(rwmi_domain* d, rwmi::PairArgs& a) {
 }
 
 rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturing) {
+  d->group_paired = 0;
   if (d->dem) return enqueue_group_dem(d, n, record, capturing);
   int b[kRoles];
   role_blocks(d, d->bs, b);
@@ -696,6 +700,7 @@ rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturin
       HIPCHK(d, rwmi::launch_pair(d->hv.has_force != 0, (int64_t)d->hv.n[0] * d->hv.n[1] % rwmi::kTile == 0, pa,
                                    d->dv, A));
       ++swaps;
+      d->group_paired += 2;
       if (count(timed, 2, 0) != RWMI_OK) return RWMI_EDEVICE;
     }
   }
@@ -1188,10 +1193,12 @@ rwmi_status rwmi_step(rwmi_domain* d, uint32_t n_steps) {
       (void)hipGraphDestroy(g);
       if (e != hipSuccess) return fail(d, RWMI_EDEVICE, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
       d->gsteps = k;
+      d->graph_paired = d->group_paired;
     }
     while (left >= d->gsteps) {
       HIPCHK(d, hipGraphLaunch(d->gexec, d->stream));
       left -= d->gsteps;
+      d->paired += d->graph_paired;
       if (d->sort_every > 0 && d->hv.nw > 0) d->sorted_at = d->steps;  // every replay sorts at its start
       d->steps += d->gsteps;
     }
@@ -1199,6 +1206,7 @@ rwmi_status rwmi_step(rwmi_domain* d, uint32_t n_steps) {
   if (left > 0) {
     if ((st = enqueue_group(d, left, d->timing, false)) != RWMI_OK) return st;
     d->steps += left;
+    d->paired += d->group_paired;
   }
   return RWMI_OK;
 }
@@ -1418,6 +1426,12 @@ rwmi_status rwmi_query_sizes(const rwmi_domain* d, uint64_t* n_nodes, uint64_t* 
   if (n_nodes) *n_nodes = (uint64_t)d->hv.N;
   if (n_walkers) *n_walkers = (uint64_t)d->hv.nw;
   if (step) *step = d->steps;
+  return RWMI_OK;
+}
+
+rwmi_status rwmi_query_paired(const rwmi_domain* d, uint64_t* updates) {
+  if (!d || !updates) return fail(nullptr, RWMI_EINVAL, "null argument");
+  *updates = d->paired;
   return RWMI_OK;
 }
 
