@@ -82,6 +82,15 @@ def walker_bytes_per_step(prec):
     return 2 * (4 + 3 * (8 if prec == "fp64" else 4))
 
 
+def credited_bytes(cfg, prec, fluid, walker, paired):
+    """Algorithmic bytes of `fluid` fluid updates and `walker` walker steps, of
+    the updates `paired` taken two per pass over the lattice, which reads and
+    writes the distributions once for both."""
+    n = fluid_nodes(cfg)
+    return (fluid * n * fluid_bytes_per_node(prec) - paired * n * 19 * ELEM[prec] +
+            walker * cfg["walkers"]["n"] * walker_bytes_per_step(prec))
+
+
 def kernel_source_hash(prec):
     """Hash of the sources the step kernel of this precision is built from."""
     h = hashlib.sha256()
@@ -165,7 +174,8 @@ def cpu_baseline(cfg, seconds=12.0, max_steps=200, single_thread=True):
 def run_plain(cfg, steps, warmup, timing=32, graph=False, burnin=0):
     """Advance `burnin` steps (untimed: the state at mid-run), warm up, then
     time `steps` steps; HIP events on the domain stream bracket windows of
-    `timing` consecutive step launches (0: none)."""
+    `timing` consecutive step launches (0: none).  Returns the seconds, the
+    timing record with the number of paired fluid updates, and the moments."""
     from paper_2308_05007_amd import binding as B
     import torch
     dom = B.build_domain(cfg, device=0)
@@ -179,12 +189,13 @@ def run_plain(cfg, steps, warmup, timing=32, graph=False, burnin=0):
     if timing:
         dom.set("timing", timing)
         dom.kernel_times()  # clear
+    paired = dom.paired()
     t0 = time.perf_counter()
     dom.step(steps)
     dom.sync()
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
-    kt = dom.kernel_times() if timing else {}
+    kt = dom.kernel_times() + (dom.paired() - paired,) if timing else {}
     mom = dom.moments()
     dom.close()
     del dom
@@ -209,23 +220,19 @@ def measure(cfg, key, steps, warmup, timing, burnin=0):
     N = int(np.prod(cfg["domain"]["n"]))
     nw = cfg["walkers"]["n"]
     assert mom["n_walkers"] == nw, "walker count not conserved"
-    ms_total, launches, fluid_launches, walker_launches = kt
-    avg_s = ms_total / 1e3 / max(launches, 1)
-    # a full launch carries one fluid update and one walker step
-    fb, wb = fluid_nodes(cfg) * fluid_bytes_per_node(prec), nw * walker_bytes_per_step(prec)
-    # unless fluid updates are taken two per pass (three launches for two
-    # steps: each step's walkers and the pair), which reads and writes the
-    # distributions once for both
-    pairs = nw > 0 and launches > 1.25 * fluid_launches > 5
-    if pairs:
-        fb -= fluid_nodes(cfg) * 19 * ELEM[prec]
-    achieved = (fluid_launches * fb + walker_launches * wb) / (ms_total / 1e3) / 1e9
+    ms_total, launches, fluid, walker, paired = kt
+    total = credited_bytes(cfg, prec, fluid, walker, paired)
+    achieved = total / (ms_total / 1e3) / 1e9
+    if paired:  # a step's walkers and the two updates' pass are launches of different work
+        bytes_launch = total // max(launches, 1)
+    else:  # a full launch carries one fluid update and one walker step
+        bytes_launch = credited_bytes(cfg, prec, 1, 1, 0)
     return {"key": key, "prec": prec, "N": N, "nw": nw, "dt": dt, "steps": steps, "burnin": burnin,
             "mlups": N * steps / dt / 1e6, "wsps": nw * steps / dt, "achieved": achieved,
-            "bytes_launch": (fluid_launches * fb + walker_launches * wb) // max(launches, 1) if pairs else fb + wb,
-            "avg_us": avg_s * 1e6, "launches": launches, "mom": mom,
-            "kernel": "k_pair (two fluid updates per pass) and k_walk (walkers, particle prologue)" if pairs else
-                      "k_step (fused: PSM-BGK collide + pull-stream, walkers, particle prologue)"}
+            "bytes_launch": bytes_launch, "avg_us": ms_total * 1e3 / max(launches, 1), "launches": launches, "mom": mom,
+            "kernel": "k_step (fused: PSM-BGK collide + pull-stream, walkers, particle prologue)" if not paired else
+                      "k_pair (two fluid updates per pass)" +
+                      (" and k_walk (walkers, particle prologue)" if nw or cfg["particles"] else "")}
 
 
 def bench_plain(args):
