@@ -686,8 +686,7 @@ rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturin
     const bool timed = record && j >= 0;
     if (a.nb[0] + a.nb[1] + a.nb[2] > 0) {
       if (begin(timed) != RWMI_OK) return RWMI_EDEVICE;
-      if (d->hv.ibb && a.nb[kRoleFluid] > 0)
-        HIPCHK(d, rwmi::launch_ibb_links(d->prec, d->dv, 0, j, false, (unsigned)a.nb[kRoleFluid], A));
+      if (d->hv.ibb) HIPCHK(d, rwmi::launch_ibb_links(d->prec, a, false, A));
       HIPCHK(d, rwmi::launch_step(d->prec, d->bs, a, A));
       if (a.nb[kRoleFluid] > 0) ++swaps;
       if (count(timed, a.nb[kRoleFluid] > 0, a.nb[kRoleWalk] > 0) != RWMI_OK) return RWMI_EDEVICE;
@@ -753,8 +752,7 @@ rwmi_status enqueue_group_dem(rwmi_domain* d, uint32_t n, bool record, bool capt
     a.j = a.s = j;
     if (a.nb[kRoleWalk] + a.nb[kRoleFluid] > 0) {
       if (open() != RWMI_OK) return RWMI_EDEVICE;
-      if (d->hv.ibb && a.nb[kRoleFluid] > 0)
-        HIPCHK(d, rwmi::launch_ibb_links(d->prec, d->dv, 0, j, true, (unsigned)a.nb[kRoleFluid], A));
+      if (d->hv.ibb) HIPCHK(d, rwmi::launch_ibb_links(d->prec, a, true, A));
       HIPCHK(d, rwmi::launch_step(d->prec, 256, a, A));
       if (close() != RWMI_OK) return RWMI_EDEVICE;
       if (record)

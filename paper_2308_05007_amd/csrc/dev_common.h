@@ -240,6 +240,12 @@ __device__ __forceinline__ uint64_t step_of(const DomView& V, int32_t k) {
   return (uint64_t)((int64_t)kp(V.tstep)[0] + k);
 }
 
+// Does a fluid update of two lattices read fB (else fA), s swaps into the launch
+// group?
+__device__ __forceinline__ bool source_lattice(const DomView& V, int32_t s) {
+  return ((kp(V.tstep)[1] + (uint64_t)s) & 1ull) != 0;
+}
+
 // Slot of the pose table and cull mask of step t.  Three slots: one launch
 // writes those of step t+1 while its fluid blocks read step t's and its
 // walker blocks step t-1's.

@@ -32,11 +32,9 @@ hipError_t noalloc_scratch(double** ptr) {
   return hipSuccess;
 }
 
-hipError_t launch_ibb_links_p64(const DomView* v, int dom, int32_t j, bool dem, unsigned blocks, hipStream_t s) {
-  if (blocks == 0) return hipSuccess;
-  blocks = kLinkGrid;  // the pass strides over the listed nodes
-  if (dem) k_ibb_links<P64, true><<<blocks, 256, 0, s>>>(v, dom, j);
-  else k_ibb_links<P64, false><<<blocks, 256, 0, s>>>(v, dom, j);
+hipError_t launch_ibb_links_p64(const StepArgs& a, bool dem, hipStream_t s) {
+  if (dem) k_ibb_links<P64, true><<<kLinkGrid, 256, 0, s>>>(a.views, a.j, a.s);
+  else k_ibb_links<P64, false><<<kLinkGrid, 256, 0, s>>>(a.views, a.j, a.s);
   return hipGetLastError();
 }
 

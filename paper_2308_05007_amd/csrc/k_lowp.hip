@@ -54,18 +54,15 @@ hipError_t launch_step_lowp(int prec, int bs, const StepArgs& a, hipStream_t s) 
 }
 
 template <int P>
-static void links(const DomView* v, int dom, int32_t j, bool dem, unsigned blocks, hipStream_t s) {
-  if (dem) k_ibb_links<P, true><<<blocks, 256, 0, s>>>(v, dom, j);
-  else k_ibb_links<P, false><<<blocks, 256, 0, s>>>(v, dom, j);
+static void links(const StepArgs& a, bool dem, hipStream_t s) {
+  if (dem) k_ibb_links<P, true><<<kLinkGrid, 256, 0, s>>>(a.views, a.j, a.s);
+  else k_ibb_links<P, false><<<kLinkGrid, 256, 0, s>>>(a.views, a.j, a.s);
 }
 
-hipError_t launch_ibb_links_lowp(int prec, const DomView* v, int dom, int32_t j, bool dem, unsigned blocks,
-                                 hipStream_t s) {
-  if (blocks == 0) return hipSuccess;
-  blocks = kLinkGrid;  // the pass strides over the listed nodes
-  if (prec == P32) links<P32>(v, dom, j, dem, blocks, s);
-  else if (prec == P16) links<P16>(v, dom, j, dem, blocks, s);
-  else links<PB16>(v, dom, j, dem, blocks, s);
+hipError_t launch_ibb_links_lowp(int prec, const StepArgs& a, bool dem, hipStream_t s) {
+  if (prec == P32) links<P32>(a, dem, s);
+  else if (prec == P16) links<P16>(a, dem, s);
+  else links<PB16>(a, dem, s);
   return hipGetLastError();
 }
 

@@ -580,17 +580,17 @@ __device__ __forceinline__ typename Store<P>::C ibb_link(const DomView& V, uint6
 // pass also clears the count of the list the fluid update of t fills.  DEM:
 // the links' momentum exchange in the block's LDS accumulator, then in the
 // step's.
-constexpr unsigned kLinkGrid = 2048;  // blocks of the link pass
+constexpr unsigned kLinkGrid = 2048;  // blocks of the link pass, which strides over the listed nodes
 constexpr int kLinkCtrl = 1024;       // control points held in LDS
 
 template <int P, bool DEM>
-__global__ void __launch_bounds__(256) k_ibb_links(const DomView* __restrict__ views, int dom, int32_t j) {
+__global__ void __launch_bounds__(256) k_ibb_links(const DomView* __restrict__ views, int32_t j, int32_t s) {
   using S = typename Store<P>::S;
   using R = typename Store<P>::C;
   using SR = typename Raw<S>::T;
   __shared__ unsigned long long dacc[DEM ? 6 * kMaxParticles : 1];
   __shared__ R cl[4 * kLinkCtrl];
-  const DomView& V = views[dom];
+  const DomView& V = views[0];
   if (V.np == 0) return;
   const uint64_t t = step_of(V, j);
   // the fluid update of t lists into [t & 1]; the pass of t - 1 has read it
@@ -602,7 +602,7 @@ __global__ void __launch_bounds__(256) k_ibb_links(const DomView* __restrict__ v
   if (first >= items) return;  // uniform over the block
   const auto list = gp((const uint32_t*)V.solid_list[(t - 1) & 1ull]);
   const auto smp = gp((const uint8_t*)V.smap[(t - 1) & 1ull]);
-  const auto src = gp((SR*)((t & 1ull) ? V.fB : V.fA));
+  const auto src = gp((SR*)(source_lattice(V, s) ? V.fB : V.fA));
   constexpr uint32_t FS = kTile;
   const auto plast = kp(V.parts) + (V.np - 1);
   const int nctl = plast->ctrl0 + plast->nc;

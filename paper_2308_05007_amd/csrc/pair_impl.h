@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a, const DomView
   const int wx = nx - x0 < a.tx ? nx - x0 : a.tx, wy = ny - y0 < a.ty ? ny - y0 : a.ty;
   const int z0 = (int)((int64_t)nz * zc / a.nzc), z1 = (int)((int64_t)nz * (zc + 1) / a.nzc);
   const uint64_t t = step_of(V, a.j);
-  const bool lat = ((kp(V.tstep)[1] + (uint64_t)a.s) & 1ull) != 0;
+  const bool lat = source_lattice(V, a.s);
   const auto src = gp((const float*)(lat ? V.fB : V.fA));
   const auto dst = gp((float*)(lat ? V.fA : V.fB));
   const auto u0 = gp((float*)V.u[t & 1ull]);

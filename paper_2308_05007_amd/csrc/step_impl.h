@@ -92,7 +92,7 @@ k_step(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict_
   else {
     const bool nt = (a.flags & kFlagNontemporal) != 0, dens = (a.flags & kFlagDensity) != 0;
     if constexpr (!IP) {
-      const bool lat = ((kp(V.tstep)[1] + (uint64_t)a.s) & 1ull) != 0;
+      const bool lat = source_lattice(V, a.s);
       fluid_block<P, BS, kTwoLattices, DEM, IBB>(V, (uint32_t)lb, t, lat, nt, dens, lds.dem);
     } else if (t & 1ull) {
       fluid_block<P, BS, kInPlaceOdd, DEM>(V, (uint32_t)lb, t, false, nt, dens, lds.dem);
