@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(THREADS) k_mom_nodes(const DomView* __restrict
   const bool stepped = done > 0;
   // the poses of the last step are still in the table its prologue (or, for
   // coupled particles, the particle update) wrote
-  if (stepped && V.np > 0 && !V.ibb) cull_block<C>(V, base, last, done - 1, sp, true);
+  if (stepped && V.np > 0 && !V.ibb) cull_block<C>(V, base, last, done - 1, sp);
   else if (threadIdx.x == 0) sp.cnt = 0;
   __syncthreads();
   double acc[kNodeMom];
@@ -544,8 +544,9 @@ __global__ void k_normals(uint32_t k0, uint32_t k1, uint32_t t, uint32_t purpose
 // A counting sort: rank within the block's bin (wave-aggregated atomics, so
 // the order inside a bin is arbitrary), exclusive scan of the bin counts,
 // scatter to scratch, copy back.  Every result of the library is independent
-// of the slot order (walker ids travel with the walkers; moments and
-// read-back go by id), so the arbitrary order inside a bin changes nothing.
+// of the slot order (walker ids travel with the walkers; read-outs put them in
+// id order and moment sums are the same in any), so the arbitrary order inside a
+// bin changes nothing.
 
 __device__ __forceinline__ uint32_t walker_bin(const DomView& V, int32_t cell) {
   const uint32_t lc = (uint32_t)cell;

@@ -6,12 +6,11 @@
 
 namespace rwmi {
 
-// walkers are float in every storage mode
 static void walk_bs(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
   switch (bs) {
-    case 128: k_walk<P32, 128><<<g, 128, 0, s>>>(a, a.views, a.boff); break;
-    case 512: k_walk<P32, 512><<<g, 512, 0, s>>>(a, a.views, a.boff); break;
-    default: k_walk<P32, 256><<<g, 256, 0, s>>>(a, a.views, a.boff); break;
+    case 128: k_walk<128><<<g, 128, 0, s>>>(a, a.views, a.boff); break;
+    case 512: k_walk<512><<<g, 512, 0, s>>>(a, a.views, a.boff); break;
+    default: k_walk<256><<<g, 256, 0, s>>>(a, a.views, a.boff); break;
   }
 }
 

@@ -104,11 +104,10 @@ __device__ __forceinline__ bool support_meets_box(const DomView& V, const int lo
 // stage their poses and control points in LDS (the moment reduction's
 // blocks).  Called by every thread of the block; wave 0 does the work,
 // taking the poses from the pose table of step t (written by the prologue of
-// an earlier launch) or, with from_table false, computing them.  Ends with
-// one block barrier.
+// an earlier launch or by the particle update).  Ends with one block barrier.
 template <typename C>
 __device__ __forceinline__ void cull_block(const DomView& V, uint32_t n0, uint32_t n1, uint64_t t,
-                                           BlockParticles<C>& sp, bool from_table) {
+                                           BlockParticles<C>& sp) {
   const int tid = threadIdx.x;
   if (tid < 64) {
     int lo[3], hi[3];
@@ -117,16 +116,12 @@ __device__ __forceinline__ void cull_block(const DomView& V, uint32_t n0, uint32
     double pc[3] = {0, 0, 0}, pv[3] = {0, 0, 0}, pw[3] = {0, 0, 0};
     const auto P = gp(V.parts) + tid;
     if (tid < V.np) {
-      if (from_table) {
-        const auto pt = gp((const double*)V.pose[pose_slot(t)]) + kPoseRec * tid;
+      const auto pt = gp((const double*)V.pose[pose_slot(t)]) + kPoseRec * tid;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          pc[a] = pt[a];
-          pv[a] = pt[3 + a];
-          pw[a] = pt[6 + a];
-        }
-      } else {
-        particle_pose(V.parts[tid], t, pc, pv);
+      for (int a = 0; a < 3; ++a) {
+        pc[a] = pt[a];
+        pv[a] = pt[3 + a];
+        pw[a] = pt[6 + a];
       }
       keep = support_meets_box(V, lo, hi, pc, P->epscut2);
     }

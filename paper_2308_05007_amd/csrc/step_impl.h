@@ -46,16 +46,16 @@ constexpr int step_waves_per_eu() {
 }
 
 // A launch without fluid blocks (steps taken in pairs, the coupled particles'
-// prologue, the ends of a group): walker and prologue blocks in the registers
-// those take.
+// prologue, the ends of a group), in the float modes, whose walkers are float in
+// every storage: walker and prologue blocks in the registers those take.
 #ifndef RWMI_WALK_WAVES
 #define RWMI_WALK_WAVES 8
 #endif
-template <int P, int BS>
-__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(P == P64 ? 1 : RWMI_WALK_WAVES)))
+template <int BS>
+__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RWMI_WALK_WAVES)))
 k_walk(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict__ boff) {
   __shared__ union {
-    WalkLds<typename Store<P>::O, BS> walk;
+    WalkLds<typename Store<P32>::O, BS> walk;
     ProLds pro;
   } lds;
   int idx = 0;
@@ -66,7 +66,7 @@ k_walk(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict_
   const DomView& V = views[d];
   const int lb = idx - bo[d];
   const uint64_t t = step_of(V, a.j);
-  if (role == kRoleWalk) walk_block<P, BS>(V, lb, t - 1, lds.walk);
+  if (role == kRoleWalk) walk_block<P32, BS>(V, lb, t - 1, lds.walk);
   else prologue_block(V, lb, t + 1, BS, lds.pro, (a.flags & kFlagDem) != 0);
 }
 
