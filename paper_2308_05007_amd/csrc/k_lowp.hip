@@ -25,7 +25,7 @@ static void step_bs(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
 
 template <int P>
 static void step_layout(int bs, unsigned g, const StepArgs& a, hipStream_t s) {
-  if (a.nb[kRoleFluid] == 0) {  // walkers and prologue only
+  if (a.nb[kRoleFluid] == 0 && (a.flags & kFlagPairs)) {  // walkers and prologue only
     walk_bs(bs, g, a, s);
     return;
   }

@@ -45,9 +45,13 @@ constexpr int step_waves_per_eu() {
   return P == P64 ? 1 : (P == P32 ? RWMI_STEP_WAVES_PER_EU_32 : RWMI_STEP_WAVES_PER_EU_16);
 }
 
-// A launch without fluid blocks (steps taken in pairs, the coupled particles'
-// prologue, the ends of a group), in the float modes, whose walkers are float in
-// every storage: walker and prologue blocks in the registers those take.
+// A launch without fluid blocks of a domain that takes fluid steps in pairs (FP32):
+// walkers and prologue at 8 waves per SIMD, 142 us for 1e7 walkers.  Such launches
+// of other domains (the ends of a group, the coupled particles' prologue) stay
+// with k_step: 8 waves leave the near-surface rows 13 spilled registers, and those
+// launches are short.  us per step of calls of one step, k_step and k_walk: 80^3
+// FP32 40.2, 42.3; 160x96x120 84.8, 88.0; 48^3 FP16 32.0 both; coupled particles
+// in calls of many steps 171.6, 173.0.
 #ifndef RWMI_WALK_WAVES
 #define RWMI_WALK_WAVES 8
 #endif

@@ -41,6 +41,10 @@ constexpr int kFlagDem = 8;
 // (lbm_impl.h); set by the host.
 constexpr int kFlagIbb = 16;
 
+// The domain takes fluid steps in pairs: launches without fluid blocks run
+// k_walk (step_impl.h); set by the host.
+constexpr int kFlagPairs = 32;
+
 // The last positions of an XCD's run hold fluid blocks only: a walker block
 // can end with a chain of near-surface evaluations (up to 10-20 us), which
 // would otherwise run on alone after the last fluid blocks.  448 is twice the
