@@ -646,6 +646,118 @@ __global__ void __launch_bounds__(256) k_ibb_links(const DomView* __restrict__ v
   }
 }
 
+// Collision of one node in float with its fused multiply-adds written out, for
+// the kernels whose values have to agree bit for bit (the single step of FP32
+// lattices that can be taken in pairs, and the pair): BGK, Guo source if
+// `force`, exchange with the solid where es > 0 (the sum of the particles' solid
+// fractions, un the sum of fraction times velocity).  put(direction, value).
+// The terms are those of the folded form in fluid_node.
+template <typename Put>
+__device__ __forceinline__ void collide_float(const DomView& V, const float (&f)[kQ], float es, const float (&un)[3],
+                                              bool force, float (&u)[3], float& rho, Put&& put) {
+  float drho = 0.0f, j[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) drho = drho + f[i];
+  rho = V.rho0_f + drho;
+  unroll<0, kQ>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (kEx[i] == 1) j[0] = j[0] + f[i]; else if constexpr (kEx[i] == -1) j[0] = j[0] - f[i];
+    if constexpr (kEy[i] == 1) j[1] = j[1] + f[i]; else if constexpr (kEy[i] == -1) j[1] = j[1] - f[i];
+    if constexpr (kEz[i] == 1) j[2] = j[2] + f[i]; else if constexpr (kEz[i] == -1) j[2] = j[2] - f[i];
+  });
+  const float ir = 1.0f / rho;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) u[a] = (j[a] + V.halfF_f[a]) * ir;
+  // the velocities are rounded values from here on (not fused into sums)
+  asm volatile("" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]));
+  const float ux = u[0], uy = u[1], uz = u[2];
+  const bool solid = es > 0.0f;
+  float B = 0.0f, A = V.omega_f, Cf = V.cfree_f, us[3] = {0.0f, 0.0f, 0.0f}, us15 = 0.0f;
+  if (solid) {
+    const float eps = es < 1.0f ? es : 1.0f;
+    B = (eps * V.tm_f) / ((1.0f - eps) + V.tm_f);
+    A = (1.0f - B) * V.omega_f;
+    Cf = (1.0f - B) * (1.0f - 0.5f * V.omega_f);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) us[a] = un[a] / es;
+    us15 = 1.5f * __builtin_fmaf(us[2], us[2], __builtin_fmaf(us[0], us[0], us[1] * us[1]));
+  }
+  asm volatile("" : "+v"(A), "+v"(Cf));
+  const float uu15 = 1.5f * __builtin_fmaf(uz, uz, __builtin_fmaf(ux, ux, uy * uy));
+  const float omA = 1.0f - A;
+  float K0 = A * __builtin_fmaf(-rho, uu15, drho);
+  const float K1 = (3.0f * A) * rho, K2 = (4.5f * A) * rho;
+  float K3 = 0.0f, K4 = 0.0f;
+  if (force) {
+    const float uF = __builtin_fmaf(uz, V.F_f[2], __builtin_fmaf(ux, V.F_f[0], uy * V.F_f[1]));
+    K3 = 9.0f * Cf;
+    K4 = 3.0f * Cf;
+    K0 = __builtin_fmaf(-K4, uF, K0);
+  }
+  const bool any_solid = __ballot(solid) != 0ull;
+  constexpr float w0 = weight<float>(0), w1 = weight<float>(1), w7 = weight<float>(7);
+  {
+    float o0 = __builtin_fmaf(f[0], omA, K0 * w0);
+    if (any_solid) {
+      const float e0 = w0 * __builtin_fmaf(rho, -uu15, drho);
+      const float x = __builtin_fmaf(B, __builtin_fmaf(w0, __builtin_fmaf(rho, -us15, drho), -e0), o0);
+      o0 = solid ? x : o0;
+    }
+    put(std::integral_constant<int, 0>{}, o0);
+  }
+  const float a1 = w1 * K1, a2 = w1 * K2, a3 = w1 * K3, a4 = w1 * K4;
+  const float b1 = w7 * K1, b2 = w7 * K2, b3 = w7 * K3, b4 = w7 * K4;
+  unroll<0, 9>([&](auto pc) {
+    constexpr int i = 1 + 2 * decltype(pc)::value;
+    constexpr int o = i + 1;
+    constexpr bool axis = i <= 6;
+    constexpr float w = axis ? w1 : w7;
+    const float eu = edot_c<i, float>(ux, uy, uz);
+    const float wK1 = axis ? a1 : b1, wK2 = axis ? a2 : b2, wK3 = axis ? a3 : b3, wK4 = axis ? a4 : b4;
+    float S, D;
+    if (force) {
+      const float eF = kp(V.eF_f)[i];
+      S = __builtin_fmaf(w, K0, eu * __builtin_fmaf(eu, wK2, eF * wK3));
+      D = __builtin_fmaf(eu, wK1, eF * wK4);
+    } else {
+      S = __builtin_fmaf(w, K0, eu * (eu * wK2));
+      D = __builtin_fmaf(eu, wK1, 0.0f);  // a product rounded on its own, not fused into S + D
+    }
+    float vi = __builtin_fmaf(f[i], omA, S + D);
+    float vo = __builtin_fmaf(f[o], omA, S - D);
+    if (any_solid) {
+      // equilibria over w: drho + rho (eu (3 +- 4.5 eu) - 1.5 u.u)
+      const float eus = edot_c<i, float>(us[0], us[1], us[2]);
+      auto eq = [&](float e, float q15) {
+        return __builtin_fmaf(rho, __builtin_fmaf(e, __builtin_fmaf(e, 4.5f, 3.0f), -q15), drho);
+      };
+      const float ti = eq(eu, uu15), to = eq(-eu, uu15), si = eq(eus, us15), so = eq(-eus, us15);
+      const float xi = __builtin_fmaf(B, __builtin_fmaf(-w, to, f[o]) - __builtin_fmaf(-w, si, f[i]), vi);
+      const float xo = __builtin_fmaf(B, __builtin_fmaf(-w, ti, f[i]) - __builtin_fmaf(-w, so, f[o]), vo);
+      vi = solid ? xi : vi;
+      vo = solid ? xo : vo;
+    }
+    put(std::integral_constant<int, i>{}, vi);
+    put(std::integral_constant<int, o>{}, vo);
+  });
+}
+
+// Sum of the solid fractions and of fraction times velocity at node nd over
+// the particles in `bits`, in index order, at the pose of slot ps.
+__device__ __forceinline__ void solid_sum(const DomView& V, int ps, unsigned long long bits, const int nd[3], float& es,
+                                          float (&un)[3]) {
+  es = un[0] = un[1] = un[2] = 0.0f;
+  while (bits) {
+    const int p = __ffsll((long long)bits) - 1;
+    bits &= bits - 1ull;
+    float v[3];
+    const float e = node_eps_direct<float>(V, ps, p, nd, v);
+    es = es + e;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) un[a] = __builtin_fmaf(e, v[a], un[a]);
+  }
+}
+
 // One node of a fluid block.  DEM: two-way coupled particles; the momentum
 // the solid term takes from the fluid at the node, -sum_i e_i B Om_i, is
 // shared among the coupled particles that cover it in proportion to their
@@ -778,9 +890,19 @@ __device__ __forceinline__ void fluid_node(const DomView& V, uint32_t lb, uint64
   // order
   R es = (R)0, unx = (R)0, uny = (R)0, unz = (R)0;
   unsigned long long cbits = 0ull;  // DEM: coupled particles that cover the node
+  // a domain that takes most steps in pairs takes some singly: the same values
+  constexpr bool paired = P == P32 && L == kTwoLattices && !DEM && !IBB;
   if (!IBB && V.np > 0) {
     const int ps = pose_slot(t);
     unsigned long long bits = kp(V.fcull[ps])[lb];
+    if constexpr (paired) {
+      float un[3];
+      solid_sum(V, ps, bits, nd, es, un);
+      unx = un[0];
+      uny = un[1];
+      unz = un[2];
+      bits = 0ull;
+    }
     while (bits) {
       const int p = __ffsll((long long)bits) - 1;
       bits &= bits - 1ull;
@@ -937,118 +1059,130 @@ __device__ __forceinline__ void fluid_node(const DomView& V, uint32_t lb, uint64
     else dst[(size_t)slot * FS + fnode(!inplace, at)] = w;
   };
 
-  // Float collision, folded: with e_o = -e_i and w_o = w_i the relaxed,
-  // forced population of an opposite pair is
-  //   (1 - A) f_i + w_i (S +- D),
-  //   S = K0 + eu (K2 eu + K3 eF),  D = eu K1 + K4 eF,
-  // eu = e_i.u, eF = e_i.F, K0 = A (drho - rho 1.5 u.u) - 3 Cf u.F,
-  // K1 = 3 A rho, K2 = 4.5 A rho, K3 = 9 Cf, K4 = 3 Cf: the same BGK and Guo
-  // terms as the FP64 form, in fewer operations.
-  R omA = (R)0, K0 = (R)0, K1 = (R)0, K2 = (R)0, K3 = (R)0, K4 = (R)0;
-  if constexpr (!exact) {
-    omA = (R)1 - A;
-    K1 = ((R)3 * A) * rho;
-    K2 = ((R)4.5 * A) * rho;
-    K0 = A * (drho - rho * uu15);
-    if (force) {
-      K3 = (R)9 * Cf;
-      K4 = (R)3 * Cf;
-      K0 = K0 - K4 * uF;
-    }
-  }
-  // rest population
-  {
-    constexpr std::integral_constant<int, 0> i0{};
-    R o0;
-    if constexpr (exact) {
-      const R fe0 = feq(i0, (R)0, uu15);
-      o0 = f[0] - A * (f[0] - fe0);
-      if (solid) o0 = o0 + B * ((f[0] - fe0) - (f[0] - feq(i0, (R)0, us15)));
-      if (force) o0 = o0 + Cf * guo(i0, (R)0);
-    } else {
-      o0 = omA * f[0] + weight<R>(0) * K0;
-      if (solid) o0 = o0 + B * (feq(i0, (R)0, us15) - feq(i0, (R)0, uu15));
-    }
-    put(i0, o0);
-  }
-  // opposite pairs (i, i+1): each pair is relaxed, exchanged with the solid,
-  // forced and stored before the next, so few registers stay live
   R hfx = (R)0, hfy = (R)0, hfz = (R)0;  // DEM: force on the solid at the node
-  unroll<0, 9>([&](auto pc) {
-    constexpr int i = 1 + 2 * decltype(pc)::value;
-    constexpr int o = i + 1;
-    constexpr std::integral_constant<int, i> ic{};
-    constexpr std::integral_constant<int, o> oc{};
-    R vi, vo;
-    if constexpr (exact) {
-      const R eui = edot_c<i, R>(ux, uy, uz);
-      const R euo = edot_c<o, R>(ux, uy, uz);
-      const R fei = feq(ic, eui, uu15);
-      const R feo = feq(oc, euo, uu15);
-      vi = f[i] - A * (f[i] - fei);
-      vo = f[o] - A * (f[o] - feo);
-      if (solid) {
-        const R fesi = feq(ic, edot_c<i, R>(usx, usy, usz), us15);
-        const R feso = feq(oc, edot_c<o, R>(usx, usy, usz), us15);
-        if constexpr (DEM) {
-          const R boi = B * ((f[o] - feo) - (f[i] - fesi));
-          const R boo = B * ((f[i] - fei) - (f[o] - feso));
-          vi = vi + boi;
-          vo = vo + boo;
-          solid_force<i, R>(boi, hfx, hfy, hfz);
-          solid_force<o, R>(boo, hfx, hfy, hfz);
-        } else {
-          vi = vi + B * ((f[o] - feo) - (f[i] - fesi));
-          vo = vo + B * ((f[i] - fei) - (f[o] - feso));
-        }
-      }
+  if constexpr (paired) {
+    const float un[3] = {unx, uny, unz};
+    float u[3];
+    collide_float(V, f, es, un, force, u, rho, [&](auto jc, float v) {
+      if (near_wall) wall_term(jc, v);
+      put(jc, v);
+    });
+    ux = u[0];
+    uy = u[1];
+    uz = u[2];
+  } else {
+    // Float collision, folded: with e_o = -e_i and w_o = w_i the relaxed,
+    // forced population of an opposite pair is
+    //   (1 - A) f_i + w_i (S +- D),
+    //   S = K0 + eu (K2 eu + K3 eF),  D = eu K1 + K4 eF,
+    // eu = e_i.u, eF = e_i.F, K0 = A (drho - rho 1.5 u.u) - 3 Cf u.F,
+    // K1 = 3 A rho, K2 = 4.5 A rho, K3 = 9 Cf, K4 = 3 Cf: the same BGK and Guo
+    // terms as the FP64 form, in fewer operations.
+    R omA = (R)0, K0 = (R)0, K1 = (R)0, K2 = (R)0, K3 = (R)0, K4 = (R)0;
+    if constexpr (!exact) {
+      omA = (R)1 - A;
+      K1 = ((R)3 * A) * rho;
+      K2 = ((R)4.5 * A) * rho;
+      K0 = A * (drho - rho * uu15);
       if (force) {
-        vi = vi + Cf * guo(ic, eui);
-        vo = vo + Cf * guo(oc, euo);
+        K3 = (R)9 * Cf;
+        K4 = (R)3 * Cf;
+        K0 = K0 - K4 * uF;
       }
-    } else {
-      // w S and w D with the weight folded into the node's constants (the
-      // products are shared by the pairs of one weight class)
-      const R eu = edot_c<i, R>(ux, uy, uz);
-      constexpr R w = weight<R>(i);
-      R S, D;
-      if (force) {
-        const R eF = kp(V.eF_f)[i];
-        S = (w * K0) + eu * ((w * K2) * eu + (w * K3) * eF);
-        D = eu * (w * K1) + (w * K4) * eF;
+    }
+    // rest population
+    {
+      constexpr std::integral_constant<int, 0> i0{};
+      R o0;
+      if constexpr (exact) {
+        const R fe0 = feq(i0, (R)0, uu15);
+        o0 = f[0] - A * (f[0] - fe0);
+        if (solid) o0 = o0 + B * ((f[0] - fe0) - (f[0] - feq(i0, (R)0, us15)));
+        if (force) o0 = o0 + Cf * guo(i0, (R)0);
       } else {
-        S = (w * K0) + eu * ((w * K2) * eu);
-        D = eu * (w * K1);
+        o0 = omA * f[0] + weight<R>(0) * K0;
+        if (solid) o0 = o0 + B * (feq(i0, (R)0, us15) - feq(i0, (R)0, uu15));
       }
-      vi = omA * f[i] + (S + D);
-      vo = omA * f[o] + (S - D);
-      if (solid) {
-        // Noble-Torczynski exchange with the solid: B ((f_o - fe_o) - (f_i - fes_i))
-        const R fei = feq(ic, eu, uu15);
-        const R feo = feq(oc, -eu, uu15);
-        const R eus = edot_c<i, R>(usx, usy, usz);
-        const R fesi = feq(ic, eus, us15);
-        const R feso = feq(oc, -eus, us15);
-        if constexpr (DEM) {
-          const R boi = B * ((f[o] - feo) - (f[i] - fesi));
-          const R boo = B * ((f[i] - fei) - (f[o] - feso));
-          vi = vi + boi;
-          vo = vo + boo;
-          solid_force<i, R>(boi, hfx, hfy, hfz);
-          solid_force<o, R>(boo, hfx, hfy, hfz);
+      put(i0, o0);
+    }
+    // opposite pairs (i, i+1): each pair is relaxed, exchanged with the solid,
+    // forced and stored before the next, so few registers stay live
+    unroll<0, 9>([&](auto pc) {
+      constexpr int i = 1 + 2 * decltype(pc)::value;
+      constexpr int o = i + 1;
+      constexpr std::integral_constant<int, i> ic{};
+      constexpr std::integral_constant<int, o> oc{};
+      R vi, vo;
+      if constexpr (exact) {
+        const R eui = edot_c<i, R>(ux, uy, uz);
+        const R euo = edot_c<o, R>(ux, uy, uz);
+        const R fei = feq(ic, eui, uu15);
+        const R feo = feq(oc, euo, uu15);
+        vi = f[i] - A * (f[i] - fei);
+        vo = f[o] - A * (f[o] - feo);
+        if (solid) {
+          const R fesi = feq(ic, edot_c<i, R>(usx, usy, usz), us15);
+          const R feso = feq(oc, edot_c<o, R>(usx, usy, usz), us15);
+          if constexpr (DEM) {
+            const R boi = B * ((f[o] - feo) - (f[i] - fesi));
+            const R boo = B * ((f[i] - fei) - (f[o] - feso));
+            vi = vi + boi;
+            vo = vo + boo;
+            solid_force<i, R>(boi, hfx, hfy, hfz);
+            solid_force<o, R>(boo, hfx, hfy, hfz);
+          } else {
+            vi = vi + B * ((f[o] - feo) - (f[i] - fesi));
+            vo = vo + B * ((f[i] - fei) - (f[o] - feso));
+          }
+        }
+        if (force) {
+          vi = vi + Cf * guo(ic, eui);
+          vo = vo + Cf * guo(oc, euo);
+        }
+      } else {
+        // w S and w D with the weight folded into the node's constants (the
+        // products are shared by the pairs of one weight class)
+        const R eu = edot_c<i, R>(ux, uy, uz);
+        constexpr R w = weight<R>(i);
+        R S, D;
+        if (force) {
+          const R eF = kp(V.eF_f)[i];
+          S = (w * K0) + eu * ((w * K2) * eu + (w * K3) * eF);
+          D = eu * (w * K1) + (w * K4) * eF;
         } else {
-          vi = vi + B * ((f[o] - feo) - (f[i] - fesi));
-          vo = vo + B * ((f[i] - fei) - (f[o] - feso));
+          S = (w * K0) + eu * ((w * K2) * eu);
+          D = eu * (w * K1);
+        }
+        vi = omA * f[i] + (S + D);
+        vo = omA * f[o] + (S - D);
+        if (solid) {
+          // Noble-Torczynski exchange with the solid: B ((f_o - fe_o) - (f_i - fes_i))
+          const R fei = feq(ic, eu, uu15);
+          const R feo = feq(oc, -eu, uu15);
+          const R eus = edot_c<i, R>(usx, usy, usz);
+          const R fesi = feq(ic, eus, us15);
+          const R feso = feq(oc, -eus, us15);
+          if constexpr (DEM) {
+            const R boi = B * ((f[o] - feo) - (f[i] - fesi));
+            const R boo = B * ((f[i] - fei) - (f[o] - feso));
+            vi = vi + boi;
+            vo = vo + boo;
+            solid_force<i, R>(boi, hfx, hfy, hfz);
+            solid_force<o, R>(boo, hfx, hfy, hfz);
+          } else {
+            vi = vi + B * ((f[o] - feo) - (f[i] - fesi));
+            vo = vo + B * ((f[i] - fei) - (f[o] - feso));
+          }
         }
       }
-    }
-    if (near_wall) {
-      wall_term(ic, vi);
-      wall_term(oc, vo);
-    }
-    put(ic, vi);
-    put(oc, vo);
-  });
+      if (near_wall) {
+        wall_term(ic, vi);
+        wall_term(oc, vo);
+      }
+      put(ic, vi);
+      put(oc, vo);
+    });
+  }
   {
     // (ux, uy, uz): three consecutive U, merged into one store by the
     // compiler; the density only where a read-out may follow

@@ -21,17 +21,18 @@
 // Measured, us per fluid step without particles, single and paired: 256^3 509 ->
 // 295, 224^3 346 -> 242, 192^3 220 -> 136; with particles a block waits at each
 // plane for the wave that evaluates their control points, where the single
-// step's other waves go on (pairs_gain).  A pass moves 1.19 times its own bytes (the rims)
-// at 5.2 TB/s; tiles 32 x 16 352, 32 x 8 423, 64 x 12 342 at 256^3, and with 4,
-// 8 runs of planes (2, 4 rounds of blocks) instead of 2 the step with particles
-// and walkers 489, 504 instead of 464.
+// step's other waves go on (pairs_gain).  A pass of 256^3 with 64 particles moves
+// 1.19 times its own bytes (the rims) at 5.2 TB/s; tiles 32 x 16 352, 32 x 8 423,
+// 64 x 12 342 at 256^3, and with 4, 8 runs of planes (2, 4 rounds of blocks)
+// instead of 2 the step with particles and walkers 489, 504 instead of 464.
 // With 16-bit storage the bytes no longer bound it and it gained nothing (281
 // against 275).  The walkers then run in a launch of their own, 142 us per step
 // for 1e7 where beside the single step's fluid they add 95: the whole step at
 // 256^3 with 1e7 walkers 607 -> 466.
 //
-// Every node is computed with the operations and roundings of the single
-// step, so a run's values do not depend on how its steps are paired.
+// Every node is computed by the functions of the single step (collide_float,
+// solid_sum), whose fused multiply-adds are written out, so a run's values do not
+// depend on how its steps are paired.
 #pragma once
 #include "lbm_impl.h"
 #include "pro_impl.h"
@@ -44,116 +45,6 @@ namespace rwmi {
 constexpr int flat_slot(int i) { return i <= 4 ? i : i - 2; }                        // 0..4, 7..10
 constexpr int up_slot(int i) { return i == 5 ? 0 : i == 11 ? 1 : i == 14 ? 2 : i == 15 ? 3 : 4; }
 static_assert(kEz[5] == 1 && kEz[11] == 1 && kEz[14] == 1 && kEz[15] == 1 && kEz[18] == 1, "directions that go up");
-
-// Collision of one node in float, written with explicit fused multiply-adds
-// (the contraction of the single step's compiled form): BGK, Guo source,
-// exchange with the solid where es > 0 (the sum of the particles' solid
-// fractions, un the sum of fraction times velocity).  put(direction, value).
-template <bool FORCE, typename Put>
-__device__ __forceinline__ void pair_collide(const DomView& V, const float (&f)[kQ], float es, const float (&un)[3],
-                                             float (&u)[3], float& rho, Put&& put) {
-  float drho = 0.0f, j[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int i = 0; i < kQ; ++i) drho = drho + f[i];
-  rho = V.rho0_f + drho;
-  unroll<0, kQ>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    if constexpr (kEx[i] == 1) j[0] = j[0] + f[i]; else if constexpr (kEx[i] == -1) j[0] = j[0] - f[i];
-    if constexpr (kEy[i] == 1) j[1] = j[1] + f[i]; else if constexpr (kEy[i] == -1) j[1] = j[1] - f[i];
-    if constexpr (kEz[i] == 1) j[2] = j[2] + f[i]; else if constexpr (kEz[i] == -1) j[2] = j[2] - f[i];
-  });
-  const float ir = 1.0f / rho;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) u[a] = (j[a] + V.halfF_f[a]) * ir;
-  // the velocities are rounded values from here on (not fused into sums)
-  asm volatile("" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]));
-  const float ux = u[0], uy = u[1], uz = u[2];
-  const bool solid = es > 0.0f;
-  float B = 0.0f, A = V.omega_f, Cf = V.cfree_f, us[3] = {0.0f, 0.0f, 0.0f}, us15 = 0.0f;
-  if (solid) {
-    const float eps = es < 1.0f ? es : 1.0f;
-    B = (eps * V.tm_f) / ((1.0f - eps) + V.tm_f);
-    A = (1.0f - B) * V.omega_f;
-    Cf = (1.0f - B) * (1.0f - 0.5f * V.omega_f);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) us[a] = un[a] / es;
-    us15 = 1.5f * __builtin_fmaf(us[2], us[2], __builtin_fmaf(us[0], us[0], us[1] * us[1]));
-  }
-  asm volatile("" : "+v"(A), "+v"(Cf));
-  const float uu15 = 1.5f * __builtin_fmaf(uz, uz, __builtin_fmaf(ux, ux, uy * uy));
-  const float omA = 1.0f - A;
-  float K0 = A * __builtin_fmaf(-rho, uu15, drho);
-  const float K1 = (3.0f * A) * rho, K2 = (4.5f * A) * rho;
-  float K3 = 0.0f, K4 = 0.0f;
-  if constexpr (FORCE) {
-    const float uF = __builtin_fmaf(uz, V.F_f[2], __builtin_fmaf(ux, V.F_f[0], uy * V.F_f[1]));
-    K3 = 9.0f * Cf;
-    K4 = 3.0f * Cf;
-    K0 = __builtin_fmaf(-K4, uF, K0);
-  }
-  const bool any_solid = __ballot(solid) != 0ull;
-  constexpr float w0 = weight<float>(0), w1 = weight<float>(1), w7 = weight<float>(7);
-  {
-    float o0 = __builtin_fmaf(f[0], omA, K0 * w0);
-    if (any_solid) {
-      const float e0 = w0 * __builtin_fmaf(rho, -uu15, drho);
-      const float x = __builtin_fmaf(B, __builtin_fmaf(w0, __builtin_fmaf(rho, -us15, drho), -e0), o0);
-      o0 = solid ? x : o0;
-    }
-    put(std::integral_constant<int, 0>{}, o0);
-  }
-  const float a1 = w1 * K1, a2 = w1 * K2, a3 = w1 * K3, a4 = w1 * K4;
-  const float b1 = w7 * K1, b2 = w7 * K2, b3 = w7 * K3, b4 = w7 * K4;
-  unroll<0, 9>([&](auto pc) {
-    constexpr int i = 1 + 2 * decltype(pc)::value;
-    constexpr int o = i + 1;
-    constexpr bool axis = i <= 6;
-    constexpr float w = axis ? w1 : w7;
-    const float eu = edot_c<i, float>(ux, uy, uz);
-    const float wK1 = axis ? a1 : b1, wK2 = axis ? a2 : b2, wK3 = axis ? a3 : b3, wK4 = axis ? a4 : b4;
-    float S, D;
-    if constexpr (FORCE) {
-      const float eF = kp(V.eF_f)[i];
-      S = __builtin_fmaf(w, K0, eu * __builtin_fmaf(eu, wK2, eF * wK3));
-      D = __builtin_fmaf(eu, wK1, eF * wK4);
-    } else {
-      S = __builtin_fmaf(w, K0, eu * (eu * wK2));
-      D = __builtin_fmaf(eu, wK1, 0.0f);  // a product rounded on its own, not fused into S + D
-    }
-    float vi = __builtin_fmaf(f[i], omA, S + D);
-    float vo = __builtin_fmaf(f[o], omA, S - D);
-    if (any_solid) {
-      // equilibria over w: drho + rho (eu (3 +- 4.5 eu) - 1.5 u.u)
-      const float eus = edot_c<i, float>(us[0], us[1], us[2]);
-      auto eq = [&](float e, float q15) {
-        return __builtin_fmaf(rho, __builtin_fmaf(e, __builtin_fmaf(e, 4.5f, 3.0f), -q15), drho);
-      };
-      const float ti = eq(eu, uu15), to = eq(-eu, uu15), si = eq(eus, us15), so = eq(-eus, us15);
-      const float xi = __builtin_fmaf(B, __builtin_fmaf(-w, to, f[o]) - __builtin_fmaf(-w, si, f[i]), vi);
-      const float xo = __builtin_fmaf(B, __builtin_fmaf(-w, ti, f[i]) - __builtin_fmaf(-w, so, f[o]), vo);
-      vi = solid ? xi : vi;
-      vo = solid ? xo : vo;
-    }
-    put(std::integral_constant<int, i>{}, vi);
-    put(std::integral_constant<int, o>{}, vo);
-  });
-}
-
-// Sum of the solid fractions and of fraction times velocity at node nd over
-// the particles in `bits`, in index order, at the pose of slot ps.
-__device__ __forceinline__ void pair_solid(const DomView& V, int ps, unsigned long long bits, const int nd[3], float& es,
-                                           float (&un)[3]) {
-  es = un[0] = un[1] = un[2] = 0.0f;
-  while (bits) {
-    const int p = __ffsll((long long)bits) - 1;
-    bits &= bits - 1ull;
-    float v[3];
-    const float e = node_eps_direct<float>(V, ps, p, nd, v);
-    es = es + e;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) un[a] = un[a] + e * v[a];
-  }
-}
 
 // ALIGNED: a plane is whole tiles of the layout (nx ny a multiple of kTile), so
 // that a node's offset within its plane is the same in every plane.
@@ -270,8 +161,8 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a, const DomView
     if (act) {
       const int nd[3] = {x, y, z};
       float es, un[3], u[3], rho;
-      pair_solid(V, ps0, bits0, nd, es, un);
-      pair_collide<FORCE>(V, f, es, un, u, rho, [&](auto ic, float v) {
+      solid_sum(V, ps0, bits0, nd, es, un);
+      collide_float(V, f, es, un, FORCE, u, rho, [&](auto ic, float v) {
         L[decltype(ic)::value * kPairRim + tid] = v;
       });
       if (inner && k >= z0 && k < z1) {
@@ -306,8 +197,8 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a, const DomView
         const uint32_t ob = ALIGNED ? byte1 : fnode(true, id) * 4u;
         const size_t oe = ALIGNED ? (size_t)((uint32_t)zb * plane) : 0;
         float es, un[3], u[3], rho;
-        pair_solid(V, ps1, bits1, nd, es, un);
-        pair_collide<FORCE>(V, g, es, un, u, rho, [&](auto ic, float v) {
+        solid_sum(V, ps1, bits1, nd, es, un);
+        collide_float(V, g, es, un, FORCE, u, rho, [&](auto ic, float v) {
           __builtin_nontemporal_store(v, at_byte<float>(dst + ((size_t)decltype(ic)::value * kTile + oe), ob));
         });
         const auto up = at_byte<float>(u1, 12u * id);
