@@ -677,7 +677,7 @@ rwmi_status enqueue_group(rwmi_domain* d, uint32_t n, bool record, bool capturin
     a.nd = 1;
     launch_roles(b, j, n, a.nb);
     // the group's last fluid step also stores the densities for read-outs
-    a.flags = launch_flags(d) | (j == (int)n - 1 ? rwmi::kFlagDensity : 0) | (pairs ? rwmi::kFlagPairs : 0);
+    a.flags = launch_flags(d) | (j == (int)n - 1 ? rwmi::kFlagDensity : 0) | (pairs && n >= 2 ? rwmi::kFlagPairs : 0);
     a.inplace = d->hv.inplace;
     a.j = j;
     a.s = (int32_t)swaps;

@@ -45,13 +45,17 @@ constexpr int step_waves_per_eu() {
   return P == P64 ? 1 : (P == P32 ? RWMI_STEP_WAVES_PER_EU_32 : RWMI_STEP_WAVES_PER_EU_16);
 }
 
-// A launch without fluid blocks of a domain that takes fluid steps in pairs (FP32):
-// walkers and prologue at 8 waves per SIMD, 142 us for 1e7 walkers.  Such launches
-// of other domains (the ends of a group, the coupled particles' prologue) stay
-// with k_step: 8 waves leave the near-surface rows 13 spilled registers, and those
-// launches are short.  us per step of calls of one step, k_step and k_walk: 80^3
-// FP32 40.2, 42.3; 160x96x120 84.8, 88.0; 48^3 FP16 32.0 both; coupled particles
-// in calls of many steps 171.6, 173.0.
+// A launch without fluid blocks of a group that takes fluid steps in pairs (FP32):
+// walkers and prologue at 8 waves per SIMD, 142 us for 1e7 walkers.  8 waves leave
+// the near-surface rows 13 spilled registers and share the L1 among more walkers,
+// so they gain where walkers are dense (the band of the oscillator) and lose where
+// they are spread.  us per step of the 256^3 oscillator, 6 waves (k_step) and 8:
+// 1e7 walkers in the band 505, 488, without particles 434, 423, with 100 times the
+// diffusivity 727, 761; 2e7 667, 632; 1e7 uniform in the box 533, 536; 5e6 460, 468.
+// Such launches of other groups (calls of one step, the coupled particles'
+// prologue) stay with k_step: 80^3 FP32 40.2, 42.3; 160x96x120 84.8, 88.0; 256^3
+// with 5e6 walkers 670, 688; 48^3 FP16 32.0 both; coupled particles in calls of
+// many steps 171.6, 173.0.
 #ifndef RWMI_WALK_WAVES
 #define RWMI_WALK_WAVES 8
 #endif

@@ -41,7 +41,7 @@ constexpr int kFlagDem = 8;
 // (lbm_impl.h); set by the host.
 constexpr int kFlagIbb = 16;
 
-// The domain takes fluid steps in pairs: launches without fluid blocks run
+// The group takes fluid steps in pairs: launches without fluid blocks run
 // k_walk (step_impl.h); set by the host.
 constexpr int kFlagPairs = 32;
 
