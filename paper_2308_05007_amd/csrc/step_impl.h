@@ -32,17 +32,22 @@ union StepLds {
 #ifndef RWMI_STEP_WAVES_PER_EU_32
 #define RWMI_STEP_WAVES_PER_EU_32 6
 #endif
+#ifndef RWMI_STEP_WAVES_PER_EU_64
+#define RWMI_STEP_WAVES_PER_EU_64 4
+#endif
 #ifndef RWMI_STEP_WAVES_PER_EU_16
 #define RWMI_STEP_WAVES_PER_EU_16 8
 #endif
-// Waves per SIMD the register allocation must leave room for, measured on
-// the 256^3 oscillator.  FP32 storage: 6 (69 VGPRs, 7 waves, no spill) runs
-// the step in 609 us against 621 us at 8 (63 VGPRs and a few spills to
-// scratch); 16-bit storage the other way round, 413 us at 8 against 431 us
-// at 6.  FP64 needs about twice the registers: no constraint.
+// Waves per SIMD the register allocation must leave room for.  FP32 storage: 6
+// (78 VGPRs, no spill); 7 (72, 2 spilled) runs most lattices within 1% of it, 160^3
+// with 6e6 walkers in 238 us instead of 233.  16-bit storage: 8, 256^3 413 us
+// against 431 at 6.  FP64: 4 (128 VGPRs, 2 spilled); the near-surface rows would
+// take 138, those of coupled particles 169, which leaves 3 and 2 waves: 64^3 with
+// 1e6 walkers 46.4 us instead of 43.9, coupled particles (120x120x180, 1e6 walkers)
+// 294.8 instead of 261.2; the smallest lattices the other way, 32^3 16.2, 16.6.
 template <int P, bool IBB = false>
 constexpr int step_waves_per_eu() {
-  return P == P64 ? 1 : (P == P32 ? RWMI_STEP_WAVES_PER_EU_32 : RWMI_STEP_WAVES_PER_EU_16);
+  return P == P64 ? RWMI_STEP_WAVES_PER_EU_64 : (P == P32 ? RWMI_STEP_WAVES_PER_EU_32 : RWMI_STEP_WAVES_PER_EU_16);
 }
 
 // A launch without fluid blocks of a group that takes fluid steps in pairs (FP32):
@@ -67,7 +72,7 @@ k_walk(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict_
     ProLds pro;
   } lds;
   int idx = 0;
-  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & 1) != 0, idx);
+  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & kFlagXcd) != 0, idx);
   if (role == kRoleNone) return;
   const int32_t* bo = boff + role * (a.nd + 1);
   const int d = find_domain(bo, a.nd, idx);
@@ -88,7 +93,7 @@ k_step(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict_
   // as restrict parameters their wave-uniform reads compile to scalar loads
   __shared__ StepLds<P, BS> lds;
   int idx = 0;
-  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & 1) != 0, idx);
+  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & kFlagXcd) != 0, idx);
   if (role == kRoleNone) return;
   const int32_t* bo = boff + role * (a.nd + 1);
   const int d = find_domain(bo, a.nd, idx);
