@@ -148,6 +148,7 @@ struct rwmi_batch {
     DomView* views = nullptr;
     int32_t* boff = nullptr;  // kRoles maps x (nd + 1)
     int blocks[kRoles] = {0, 0, 0};
+    bool tail = false;
   };
   std::vector<Group> groups;
   std::vector<void*> owned;
@@ -595,10 +596,13 @@ bool sort_before(const rwmi_domain* d, uint32_t j, uint32_t n, bool capturing) {
 // end of the group, so it times step launches only.
 rwmi_status enqueue_group_dem(rwmi_domain* d, uint32_t n, bool record, bool capturing);
 
+// The role map with a tail of fluid blocks (step_map.h)?
+bool tail_map(int64_t particles, int64_t walkers, int64_t nodes) { return particles > 0 || walkers <= nodes; }
+
 // Flags of a domain's step launches: the caller's, plus the coupling's
-// (interpolated bounce-back reads every step's densities).
+// (interpolated bounce-back reads every step's densities) and the role map's.
 int launch_flags(const rwmi_domain* d) {
-  return d->flags | (d->hv.ibb ? rwmi::kFlagIbb | rwmi::kFlagDensity : 0);
+  return d->flags | (d->hv.ibb ? rwmi::kFlagIbb | rwmi::kFlagDensity : 0) | (tail_map(d->hv.np, d->hv.nw, d->hv.N) ? rwmi::kFlagTail : 0);
 }
 
 // Fluid steps in pairs (pair_impl.h)?  The byte offsets of the lattice and the
@@ -1987,7 +1991,7 @@ static rwmi_status batch_rebuild(rwmi_batch* b) {
     const int nd = (int)g.doms.size();
     std::vector<DomView> hv(nd);
     std::vector<int32_t> boff(kRoles * (nd + 1));
-    int64_t acc[kRoles] = {0, 0, 0};
+    int64_t acc[kRoles] = {0, 0, 0}, np = 0, nw = 0, N = 0;
     for (int i = 0; i < nd; ++i) {
       int bl[kRoles];
       role_blocks(g.doms[i], gbs, bl);
@@ -1996,7 +2000,11 @@ static rwmi_status batch_rebuild(rwmi_batch* b) {
         acc[k] += bl[k];
       }
       hv[i] = g.doms[i]->hv;
+      np += hv[i].np;
+      nw += hv[i].nw;
+      N += hv[i].N;
     }
+    g.tail = tail_map(np, nw, N);
     for (int k = 0; k < kRoles; ++k) {
       if (acc[k] > (int64_t)1 << 28) return bfail(b, RWMI_EINVAL, "batch too large for one launch");
       boff[k * (nd + 1) + nd] = (int32_t)acc[k];
@@ -2037,7 +2045,7 @@ static rwmi_status batch_enqueue_group(rwmi_batch* b, uint32_t n, bool capturing
       a.boff = g.boff;
       a.nd = (int)g.doms.size();
       launch_roles(g.blocks, j, n, a.nb);
-      a.flags = b->flags | (j == (int)n - 1 ? rwmi::kFlagDensity : 0);
+      a.flags = b->flags | (j == (int)n - 1 ? rwmi::kFlagDensity : 0) | (g.tail ? rwmi::kFlagTail : 0);
       a.inplace = g.inplace;
       a.j = a.s = j;
       if (a.nb[0] + a.nb[1] + a.nb[2] == 0) continue;

@@ -93,7 +93,8 @@ k_step(StepArgs a, const DomView* __restrict__ views, const int32_t* __restrict_
   // as restrict parameters their wave-uniform reads compile to scalar loads
   __shared__ StepLds<P, BS> lds;
   int idx = 0;
-  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & kFlagXcd) != 0, idx);
+  const int role = step_role((int)blockIdx.x, a.nb, (a.flags & kFlagXcd) != 0, idx,
+                             (a.flags & kFlagTail) != 0 ? kTailBlocks : 0);
   if (role == kRoleNone) return;
   const int32_t* bo = boff + role * (a.nd + 1);
   const int d = find_domain(bo, a.nd, idx);

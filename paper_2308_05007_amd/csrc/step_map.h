@@ -45,16 +45,22 @@ constexpr int kFlagIbb = 16;
 // k_walk (step_impl.h); set by the host.
 constexpr int kFlagPairs = 32;
 
-// The last positions of an XCD's run hold fluid blocks only: a walker block
-// can end with a chain of near-surface evaluations (up to 10-20 us), which
-// would otherwise run on alone after the last fluid blocks.  448 is twice the
+// With particles, the last positions of an XCD's run hold fluid blocks only: a
+// walker block can end with a chain of near-surface evaluations (up to 10-20 us),
+// which would otherwise run on alone after the last fluid blocks.  448 is twice the
 // blocks of 256 threads an XCD holds at once (32 CUs, 7 blocks), some 12 us of
 // fluid.  us per step with the walkers spread over the whole run, and with the
 // last 224, 448 and 896 positions left out: 128^3 FP32 channel 65.9, 62.7,
 // 61.5, 65.9; 192^3 FP32 bounce-back 297.4, 293.7, 290.9, 291.3; 80^3 FP32
 // 26.1, 23.5, 24.0, 24.0; 97x61x83 FP64 41.6, 35.5, 35.7, 35.7; 256^3 within
 // 1%.  (Walkers all first, which the smallest grids get: they fit the chip.)
+// Without particles there is no such chain, and with more walkers than nodes the
+// fluid left for the end is missed beside the walkers: spread and with 448 left
+// out, 96^3 FP32 with 3e6 walkers 56.4, 62.5; with 9e5 35.7, 36.4; 128^3 with 2e6
+// 77.2, 76.3, with 3e4 55.6, 54.5; 48^3 with 1e5 8.5, 8.1; 256^3 FP16 with 1e5 297,
+// 288.
 constexpr int kTailBlocks = 448;
+constexpr int kFlagTail = 64;  // the launch has particles, or no more walkers than nodes; set by the host
 
 struct DomView;
 
@@ -129,7 +135,7 @@ RWMI_HD inline int step_grid(const int nb[3], bool xcd) {
 
 // Role of hardware block i and its index among the blocks of that role
 // (kRoleNone for the padding blocks of the XCD-aware grid).
-RWMI_HD inline int step_role(int i, const int nb[3], bool xcd, int& idx) {
+RWMI_HD inline int step_role(int i, const int nb[3], bool xcd, int& idx, int tail = kTailBlocks) {
   int g = i, cw = nb[0], cp = nb[1], cf = nb[2], bw = 0, bp = 0, bf = 0;
   if (xcd) {
     const int x = i & 7;
@@ -149,7 +155,7 @@ RWMI_HD inline int step_role(int i, const int nb[3], bool xcd, int& idx) {
   if (h >= T) return kRoleNone;
   // walker blocks spread evenly over the first S positions: position h < S is
   // a walker block when floor((h+1) cw / S) > floor(h cw / S)
-  const int tail = xcd ? kTailBlocks : 8 * kTailBlocks;
+  if (!xcd) tail *= 8;
   const int S = T - tail > cw ? T - tail : cw;
   if (h >= S) {
     idx = bf + (h - cw);
